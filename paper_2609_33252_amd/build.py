@@ -18,11 +18,13 @@ OUT = os.path.join(HERE, "libcep.so")
 OBJ = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
-SOURCES = ["route.hip", "gemm.hip", "gemm_bf16.hip", "gemm_fp8.hip", "gemm_mx.hip", "runtime.hip", "profile.cpp", "oewf.cpp"]
-# Per-source extra flags.  The e4m3 GEMM promotes every MFMA result with
+SOURCES = ["route.hip", "gemm.hip", "gemm_bf16.hip", "gemm_fp8.hip", "gemm_mx.hip",
+           "gemm_rows.hip", "runtime.hip", "profile.cpp", "oewf.cpp"]
+# Per-source extra flags.  The e4m3 GEMMs promote every MFMA result with
 # VALU arithmetic; taking MFMA results in VGPRs saves one accvgpr read per
 # promoted element.
-EXTRA = {"gemm_fp8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {"gemm_fp8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "gemm_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 # -packed-fp32-ops: keep the compiler from forming v_pk_{add,mul,fma}_f32.
 CFLAGS = ["-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", f"--offload-arch={ARCH}",

@@ -87,15 +87,9 @@ constexpr int kBf16SmallTileM = 64;  // bf16 tile for batches with few rows per 
 // rows instead of once per 64)
 constexpr int kBf16VarTileM = 128;
 constexpr int kBf16VarMinRows = 64;
-inline bool batch_var_tiles(int wk, int align, int pairs, int n_experts) {
-  return wk == kWBf16 && align == kBf16SmallTileM && pairs >= kBf16VarMinRows * n_experts;
-}
-// Smaller bf16 batches stream the weights: GEMM1 runs the 64-row tiles
-// ordered by rows (most first) in 64-column work items handed to free CUs
-// in that order (launch_bf16_stream), GEMM2 the 64-row tiles as listed.
-inline bool batch_stream_tiles(int wk, int align, int pairs, int n_experts) {
-  return wk == kWBf16 && align == kBf16SmallTileM && pairs < kBf16VarMinRows * n_experts;
-}
+// e4m3 / MXFP4 batches of row alignment 128 with fewer pairs per local expert
+// than this run in 64-row tiles
+constexpr int kRowsSmallTile = 64;
 
 // Per-expert row alignment A of one batch's grouped layout = M tile of the
 // GEMMs that run it.  bf16 batches with fewer than one large tile of rows
@@ -105,6 +99,23 @@ inline bool batch_stream_tiles(int wk, int align, int pairs, int n_experts) {
 inline int batch_align(int wk, int pairs, int n_experts) {
   if (wk != kWBf16) return pairs >= kFp8LargeTileM * n_experts ? kFp8LargeTileM : kFp8TileM;
   return pairs >= kBf16TileM * n_experts ? kBf16TileM : kBf16SmallTileM;
+}
+// The scan's second tile list of each kind (resident / fetched experts):
+// none; kListVar 128-row tiles (64-row alignment); kListSorted the same tiles
+// ordered by rows, most first; kListHalf 64-row tiles (128-row alignment).
+enum : int { kListNone = 0, kListVar = 1, kListSorted = 2, kListHalf = 3 };
+inline int batch_list2(int wk, int align, int pairs, int n_experts) {
+  if (wk != kWBf16)
+    return align == kFp8TileM && pairs < kRowsSmallTile * n_experts ? kListHalf : kListNone;
+  if (align != kBf16SmallTileM) return kListNone;
+  // smaller bf16 batches stream the weights: both GEMMs run the 64-row tiles
+  // ordered by rows, one work item per workgroup in that order
+  return pairs >= kBf16VarMinRows * n_experts ? kListVar : kListSorted;
+}
+// Upper bound of a batch's M tiles: the GEMMs' grids
+inline int batch_tiles(int align, int list2, int pairs, int n_experts) {
+  const int m = list2 == kListHalf ? 64 : align;
+  return (pairs + m - 1) / m + n_experts;
 }
 constexpr int kMinAlign = 64;
 constexpr int kMaxAlign = 256;
@@ -179,7 +190,7 @@ struct Scratch {
   int32_t *off_pad;    // [E+1]
   Tile *tiles;         // [4][max_tiles]: list 2*f + r for resident (f = 0) or
                        // fetched (f = 1) experts; r = 1: 64-row remainder tiles
-                       // (256-row batches) or 128-row tiles (batch_var_tiles)
+                       // (256-row batches) or batch_list2's tiles
   int32_t *n_tiles;    // [4]
   int32_t *pos_of;     // [max_rows * k] grouped row of each flat pair or -1
   int32_t *perm;       // [max_mpad] flat pair of each grouped row or -1
@@ -239,11 +250,8 @@ hipError_t launch_ingest(const Arena &a, const IngestGroup &grp, int k, int E, i
 // split_cu > 0 (bf16 batches with 256-row tiles): the scan may move each
 // expert's last partial tile of at most 128 rows to 64-row remainder tiles
 // when its makespan estimate for split_cu compute units and GEMM1's
-// n_tiles_n 256-wide column tiles improves.  list2: the scan also lists,
-// in the second list of each kind, the 128-row tiles (kListVar,
-// batch_var_tiles) or the same tiles ordered by rows, most first
-// (kListSorted, batch_stream_tiles).
-enum : int { kListNone = 0, kListVar = 1, kListSorted = 2 };
+// n_tiles_n 256-wide column tiles improves.  list2: the scan's second list of
+// each kind (batch_list2).
 hipError_t launch_route(const Arena &a, const Scratch &sc, int row0, int n_rows, int k, int E,
                         int align, int expected_pairs, int max_mpad, int max_tiles,
                         uint64_t fetched_mask, int x_dtype, int wk, int d, int split_cu,
@@ -260,19 +268,18 @@ hipError_t launch_combine(const Arena &a, const Scratch &sc, int row0, int n_row
 // split_tiles > 0, up to split_tiles 64-row remainder tiles
 // gather (bf16 weights and rows only): GEMM1 reads the batch's input rows
 // (arena rows from row0) in place through the permutation instead of a
-// packed copy.  var: both GEMMs run the 128-row tile list instead.
-// stream (batch_stream_tiles, the scan run with kListSorted): both GEMMs
-// run the sorted tile list (launch_bf16_stream, launch_bf16_stream2).
+// packed copy.  list2 (batch_list2, the scan run with the same): with
+// kListVar, kListSorted and kListHalf both GEMMs run the second list's tiles.
 hipError_t launch_gemm1(const Scratch &sc, int which, int list_cap, int grid_tiles,
-                        int split_tiles, int align, bool var, bool stream, const BlobTable &bt,
-                        const BlobLayout &L, int wk, int d, int I, const Arena *gather, int row0,
+                        int split_tiles, int align, int list2, const BlobTable &bt, const BlobLayout &L,
+                        int wk, int d, int I, const Arena *gather, int row0,
                         int k, hipStream_t s);
 // out (may be null): with gemm2_writes_solo, a grouped row whose token
 // has no other local pair (Scratch::ydst) is written to that token's output
 // row [d] float32 as the combine would write it, instead of to y.
 hipError_t launch_gemm2(const Scratch &sc, int which, int list_cap, int grid_tiles,
-                        int split_tiles, int align, bool var, bool stream, const BlobTable &bt,
-                        const BlobLayout &L, int wk, int d, int I, float *out, hipStream_t s);
+                        int split_tiles, int align, int list2, const BlobTable &bt, const BlobLayout &L,
+                        int wk, int d, int I, float *out, hipStream_t s);
 // GEMM2 writes single-pair tokens' output rows itself, except in the 256-row
 // bf16 tiles (batches of row alignment kBf16TileM, and their remainders).
 inline bool gemm2_writes_solo(int wk, int align) { return wk != kWBf16 || align != kBf16TileM; }

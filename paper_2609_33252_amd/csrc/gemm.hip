@@ -2,7 +2,7 @@
 // invocations"): GEMM1 = gate/up projection with SwiGLU (and, for e4m3
 // and MXFP4 weights, the h re-quantisation) in the epilogue; GEMM2 = down
 // projection scaled by each row's routing coefficient.  Kernels:
-// gemm_bf16.hip, gemm_fp8.hip, gemm_mx.hip.
+// gemm_bf16.hip, gemm_fp8.hip, gemm_mx.hip, gemm_rows.hip.
 #include "gemm_common.h"
 
 namespace cep {
@@ -21,9 +21,11 @@ GemmArgs base_args(const Scratch &sc, int list, int list_cap, int grid_tiles,
 
 template <bool SWIGLU>
 hipError_t launch_any(const GemmArgs &g, int grid_tiles, int split_tiles, int align, int wk,
-                      const Scratch &sc, int which, int list_cap, hipStream_t s) {
-  if (wk == kWFp8) return launch_fp8<SWIGLU>(g, grid_tiles, align, s);
-  if (wk == kWMx) return launch_mx<SWIGLU>(g, grid_tiles, align, s);
+                      bool small, const Scratch &sc, int which, int list_cap, hipStream_t s) {
+  if (wk != kWBf16 && align == kFp8TileM)
+    return launch_rows<SWIGLU>(g, grid_tiles, wk == kWFp8, small, s);
+  if (wk == kWFp8) return launch_fp8<SWIGLU>(g, grid_tiles, s);
+  if (wk == kWMx) return launch_mx<SWIGLU>(g, grid_tiles, s);
   hipError_t e = launch_bf16<SWIGLU>(g, grid_tiles, align, s);
   if (e != hipSuccess || split_tiles <= 0) return e;
   // remainder tiles: same operands and output, the 64-row list
@@ -34,9 +36,8 @@ hipError_t launch_any(const GemmArgs &g, int grid_tiles, int split_tiles, int al
   return launch_bf16_rem<SWIGLU>(r, split_tiles, s);
 }
 
-// the scan's second list of `which`: the batch's 128-row tiles (kListVar)
-// or its 64-row tiles ordered by rows (kListSorted)
-GemmArgs var_list(GemmArgs g, const Scratch &sc, int which, int list_cap) {
+// the scan's second list of `which` (batch_list2)
+GemmArgs second_list(GemmArgs g, const Scratch &sc, int which, int list_cap) {
   g.tiles = sc.tiles + (size_t)(2 * which + 1) * list_cap;
   g.n_tiles = sc.n_tiles + 2 * which + 1;
   return g;
@@ -45,8 +46,8 @@ GemmArgs var_list(GemmArgs g, const Scratch &sc, int which, int list_cap) {
 }  // namespace
 
 hipError_t launch_gemm1(const Scratch &sc, int which, int list_cap, int grid_tiles,
-                        int split_tiles, int align, bool var, bool stream, const BlobTable &bt,
-                        const BlobLayout &L, int wk, int d, int I, const Arena *gather, int row0,
+                        int split_tiles, int align, int list2, const BlobTable &bt, const BlobLayout &L,
+                        int wk, int d, int I, const Arena *gather, int row0,
                         int k, hipStream_t s) {
   if (grid_tiles <= 0) return hipSuccess;
   GemmArgs g = base_args(sc, 2 * which, list_cap, grid_tiles, bt);
@@ -65,14 +66,16 @@ hipError_t launch_gemm1(const Scratch &sc, int which, int list_cap, int grid_til
   g.bs_off = L.s1_off;
   g.out = sc.h;
   g.out_s = sc.hs;
-  if (var) return launch_bf16_var<true>(var_list(g, sc, which, list_cap), grid_tiles, s);
-  if (stream) return launch_bf16_stream(var_list(g, sc, which, list_cap), grid_tiles, s);
-  return launch_any<true>(g, grid_tiles, split_tiles, align, wk, sc, which, list_cap, s);
+  if (list2 != kListNone) g = second_list(g, sc, which, list_cap);
+  if (list2 == kListVar) return launch_bf16_var<true>(g, grid_tiles, s);
+  if (list2 == kListSorted) return launch_bf16_stream(g, grid_tiles, s);
+  return launch_any<true>(g, grid_tiles, split_tiles, align, wk, list2 == kListHalf, sc, which,
+                          list_cap, s);
 }
 
 hipError_t launch_gemm2(const Scratch &sc, int which, int list_cap, int grid_tiles,
-                        int split_tiles, int align, bool var, bool stream, const BlobTable &bt,
-                        const BlobLayout &L, int wk, int d, int I, float *out, hipStream_t s) {
+                        int split_tiles, int align, int list2, const BlobTable &bt, const BlobLayout &L,
+                        int wk, int d, int I, float *out, hipStream_t s) {
   if (grid_tiles <= 0) return hipSuccess;
   GemmArgs g = base_args(sc, 2 * which, list_cap, grid_tiles, bt);
   if (out && gemm2_writes_solo(wk, align)) {
@@ -87,9 +90,11 @@ hipError_t launch_gemm2(const Scratch &sc, int which, int list_cap, int grid_til
   g.bs_off = L.s2_off;
   g.out = sc.y;
   g.wrow = sc.wrow;
-  if (var) return launch_bf16_var<false>(var_list(g, sc, which, list_cap), grid_tiles, s);
-  if (stream) return launch_bf16_stream2(var_list(g, sc, which, list_cap), grid_tiles, s);
-  return launch_any<false>(g, grid_tiles, split_tiles, align, wk, sc, which, list_cap, s);
+  if (list2 != kListNone) g = second_list(g, sc, which, list_cap);
+  if (list2 == kListVar) return launch_bf16_var<false>(g, grid_tiles, s);
+  if (list2 == kListSorted) return launch_bf16_stream2(g, grid_tiles, s);
+  return launch_any<false>(g, grid_tiles, split_tiles, align, wk, list2 == kListHalf, sc, which,
+                          list_cap, s);
 }
 
 }  // namespace cep

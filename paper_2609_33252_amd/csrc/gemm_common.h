@@ -66,26 +66,12 @@ __device__ inline void tile_of(int L, int n_live, int n_tiles_n, int *mt, int *n
   }
 }
 
-// Work item of this workgroup, balanced over the XCDs.  The grid covers the
-// host's upper bound on M tiles; the live count is on the device.  The live
-// work W = n_live x N tiles is cut into 8 contiguous shares, one per XCD
+// Work item it of this workgroup, balanced over the XCDs.  The grid covers
+// the host's upper bound on M tiles; the live count is on the device.  The
+// live work W = n_live x N tiles is cut into 8 contiguous shares, one per XCD
 // (workgroup ids are dispatched round-robin over the XCDs), so the surplus
 // workgroups of the bound never leave an XCD idle while another holds the
-// tail.  Returns false for a surplus workgroup.
-template <int GM>
-__device__ inline bool balanced_tile(int n_live, int n_tiles_n, int *mt, int *nt) {
-  const int W = n_live * n_tiles_n;
-  const int C = (W + 7) / 8;
-  const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int L = x * C + j;
-  if (j >= C || L >= W) return false;
-  tile_of<GM>(L, n_live, n_tiles_n, mt, nt);
-  return true;
-}
-
-// Work item it of this workgroup, balanced over the XCDs as balanced_tile:
-// the live work W = n_live x N tiles is cut into 8 contiguous shares, one per
-// XCD.  A persistent grid (one workgroup per CU, gridDim.x a multiple of 8)
+// tail.  A persistent grid (one workgroup per CU, gridDim.x a multiple of 8)
 // takes items j, j + gridDim.x/8, ... of its XCD's share; otherwise a
 // workgroup takes item blockIdx.x/8 only.
 template <int GM, bool PERSIST>
@@ -114,7 +100,7 @@ inline int persistent_grid() {
   return cached[dev];
 }
 
-// Grid for balanced_tile: at least the bound's work, a multiple of 8.
+// Grid for work_item: at least the bound's work, a multiple of 8.
 inline int balanced_grid(int grid_tiles, int gm, int n_tiles_n) {
   return ((grid_tiles + gm - 1) / gm * gm * n_tiles_n + 7) / 8 * 8;
 }
@@ -255,30 +241,6 @@ __device__ inline void wait_stages(int r) {
 // 4*(l/16) + r of the 256-column tile nt (lane l), so each lane holds four
 // consecutive outputs of a row.
 //
-// GEMM2: the routing coefficients of the lane's eight rows, loaded before
-// the K loop so that their latency hides behind it (loaded in the epilogue,
-// each load's wait would also wait for the stores before it).
-__device__ inline void load_row_coef(const GemmArgs &g, const Tile &t, int wm, int lane,
-                                     float (&wr)[8]) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int rt = wm * 128 + i * 16 + (lane & 15);
-    wr[i] = rt < t.rows ? g.wrow[(size_t)t.row0 + rt] : 0.0f;
-  }
-}
-
-// GEMM2: the output rows of the lane's eight rows for a direct write
-// (GemmArgs::ydst), -1 for a grouped output row; loaded with the
-// coefficients.
-__device__ inline void load_row_dst(const GemmArgs &g, const Tile &t, int wm, int lane,
-                                    int (&yd)[8]) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int rt = wm * 128 + i * 16 + (lane & 15);
-    yd[i] = g.ydst && rt < t.rows ? g.ydst[(size_t)t.row0 + rt] : -1;
-  }
-}
-
 // The bits of +0.0f + x for the float with bits x: -0 becomes +0.  A token's
 // only grouped output, written as its output row, gets the bits the combine's
 // float32 sum from +0 would give it.
@@ -290,39 +252,6 @@ __device__ inline void widen_bf16x8(const u32x4 &v, u32x4 &lo, u32x4 &hi) {
              plus_zero(v.y & 0xffff0000u)};
   hi = u32x4{plus_zero(v.z << 16), plus_zero(v.z & 0xffff0000u), plus_zero(v.w << 16),
              plus_zero(v.w & 0xffff0000u)};
-}
-
-// GEMM2: y = coefficient * acc in bf16, four consecutive columns (8 bytes)
-// per lane and row; a row with yd[i] >= 0 goes to that output row as float32
-// (16 bytes).
-__device__ inline void store_y_bf16(const f32x4 (&acc)[8][4], const float (&wrow)[8],
-                                    const int (&yd)[8], const GemmArgs &g, const Tile &t, int nt,
-                                    int wm, int wn, int lane) {
-  __bf16 *Y = (__bf16 *)g.out;
-  const int r16 = lane & 15, grp = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int rt = wm * 128 + i * 16 + r16;
-    if (rt >= t.rows) continue;
-    const size_t row = (size_t)t.row0 + rt;
-    const float wr = wrow[i];
-    const size_t col = (size_t)nt * 256 + wn * 64 + 4 * grp;
-    __bf16 *yrow = Y + row * g.N + col;
-    uint32_t *orow = yd[i] >= 0 ? (uint32_t *)g.yout + (size_t)yd[i] * g.N + col : nullptr;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t v[2];
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-        v[r] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)(acc[i][j][2 * r] * wr)) |
-               ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)(acc[i][j][2 * r + 1] * wr)) << 16);
-      if (orow)
-        *(u32x4 *)(orow + j * 16) = u32x4{plus_zero(v[0] << 16), plus_zero(v[0] & 0xffff0000u),
-                                          plus_zero(v[1] << 16), plus_zero(v[1] & 0xffff0000u)};
-      else
-        *(uint2 *)(yrow + j * 16) = make_uint2(v[0], v[1]);
-    }
-  }
 }
 
 // GEMM2 outputs y = coefficient * acc of a wave's 8 x 4 fragments, rounded
@@ -351,13 +280,13 @@ __device__ inline void pack_y_bf16(const f32x4 (&acc)[8][4], const float (&wrow)
 // staged as rows 0-63 in lo and 64-127 in hi (32 KB each).  The barriers
 // wait for LDS operations only: loads and stores in flight (the previous
 // pass's stores, a persistent workgroup's prefetch of its next tile) are not
-// waited for.  FULL stores the padding rows of the tile too (never read), so
+// waited for.  The padding rows of the tile are stored too (never read), so
 // that every wave issues at least a fixed number of stores.  sD (LDS) holds
 // the tile rows' GemmArgs::ydst: a row with sD[row] >= 0 goes to that output
 // row as float32 (two 16-byte stores per piece), padding rows have -1.
-// Returns a lower bound of the store instructions the wave issued (FULL): a
+// Returns a lower bound of the store instructions the wave issued: a
 // piece's store instructions run only for lanes that take their branch.
-template <int NW, bool FULL = false>
+template <int NW>
 __device__ inline int store_y_bf16_staged(const uint32_t (&yb)[8][4][2], const GemmArgs &g,
                                           const Tile &t, int nt, int wm, int wn, int lane,
                                           int tid, u32x4 *lo, u32x4 *hi, const int *sD) {
@@ -387,7 +316,6 @@ __device__ inline int store_y_bf16_staged(const uint32_t (&yb)[8][4][2], const G
 #pragma unroll 4
     for (int q = tid; q < 128 * 32; q += 64 * NW) {
       const int lr = q >> 5, c = q & 31, row = pass * 128 + lr;
-      if (!FULL && row >= t.rows) break;  // q grows with the row
       const u32x4 *src = lr < 64 ? lo : hi;
       const int pr = lr & 63;
       const u32x4 v = src[pr * 32 + (c ^ (pr & 15))];
@@ -418,8 +346,8 @@ __device__ inline int store_y_bf16_staged(const uint32_t (&yb)[8][4][2], const G
 // c of row r at slot c ^ ((r >> 1) & 7): a write instruction's sixteen rows x
 // four dwords hit distinct banks), then the workgroup stores whole 128-byte
 // row segments with 16-byte stores.  st holds BM x 128 bytes.  Barriers and
-// FULL as in store_y_bf16_staged.
-template <int NW, bool FULL = false>
+// padding rows as in store_y_bf16_staged.
+template <int NW>
 __device__ inline void store_h_mx_staged(const f32x4 (&acc)[8][4], const GemmArgs &g,
                                          const Tile &t, int nt, int wm, int wn, int lane,
                                          int tid, u32x4 *st) {
@@ -466,7 +394,6 @@ __device__ inline void store_h_mx_staged(const f32x4 (&acc)[8][4], const GemmArg
 #pragma unroll 2
   for (int q = tid; q < BM * 8; q += 64 * NW) {
     const int row = q >> 3, c = q & 7;
-    if (!FULL && row >= t.rows) break;  // q grows with the row
     *(u32x4 *)(H + (size_t)row * I + c * 16) = st[row * 8 + (c ^ ((row >> 1) & 7))];
   }
   // the scales last (a store before the barrier would make it wait for
@@ -500,8 +427,12 @@ hipError_t launch_bf16_stream(const GemmArgs &g, int grid_tiles, hipStream_t s);
 // bf16 GEMM2 of a weight-streaming batch over the same list, 128-column items
 hipError_t launch_bf16_stream2(const GemmArgs &g, int grid_tiles, hipStream_t s);
 template <bool SWIGLU>
-hipError_t launch_fp8(const GemmArgs &g, int grid_tiles, int align, hipStream_t s);
+hipError_t launch_fp8(const GemmArgs &g, int grid_tiles, hipStream_t s);
 template <bool SWIGLU>
-hipError_t launch_mx(const GemmArgs &g, int grid_tiles, int align, hipStream_t s);
+hipError_t launch_mx(const GemmArgs &g, int grid_tiles, hipStream_t s);
+// e4m3 (fp8) or MXFP4 GEMM of a batch of row alignment 128: its 64-row
+// (small) or 128-row tiles
+template <bool SWIGLU>
+hipError_t launch_rows(const GemmArgs &g, int grid_tiles, bool fp8, bool small, hipStream_t s);
 
 }  // namespace cep

@@ -22,6 +22,7 @@
 #include "gemm_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace cep {
 namespace {
@@ -42,10 +43,11 @@ __device__ inline f32x4 f8_mfma(const i32x8 &w, const i32x8 &x, int ox, int sx) 
   }
 }
 
-// BM x 256 output tile, K step 128 (one weight scale block).  NW waves: four
-// column groups of 64 x (NW/4) row groups of 128, each wave owning 128 rows x
-// 64 columns = 8 x 4 16x16 fragments.  With 8 waves (two per SIMD) one wave's
-// promotion overlaps the other's MFMAs.
+// 256 x 256 output tile, K step 128 (one weight scale block).  8 waves: four
+// column groups of 64 x two row groups of 128, each wave owning 128 rows x 64
+// columns = 8 x 4 16x16 fragments.  With two waves per SIMD one wave's
+// promotion overlaps the other's MFMAs.  (Batches of fewer rows per expert:
+// gemm_rows.hip.)
 //
 // Operands stream through a ring of STAGES LDS stages filled by direct
 // global->LDS loads issued STAGES-1 steps ahead ((BM + 256) x 128 codes plus
@@ -59,7 +61,7 @@ __device__ inline f32x4 f8_mfma(const i32x8 &w, const i32x8 &x, int ox, int sx) 
 // 2-4) has one parity, and those lanes then touch sixteen distinct slots of
 // 256 bytes.
 //
-// PERSIST (8 waves, two stages): one workgroup per CU takes work items j,
+// Persistent: one workgroup per CU takes work items j,
 // j + grid/8, ... of its XCD's share.  After a tile's K loop it issues the
 // next tile's first stage into buffer 0 and loads the next tile's block
 // scales into registers, then runs the epilogue through buffer 1 (staged
@@ -76,20 +78,17 @@ struct F8Tile {
   const float *bs;
 };
 
-template <int NW, int STAGES, bool SWIGLU, bool PERSIST, int OCC = 1>
-__global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
+template <bool SWIGLU>
+__global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
+  constexpr int NW = 8, STAGES = 2;
   constexpr int BM = 128 * NW / 4, BN = 256, BK = 128, WN = BN / 4;
   constexpr int A_LD = BM * BK / 1024 / NW, B_LD = BN * BK / 1024 / NW;  // loads per wave
   constexpr int PER = A_LD + B_LD;  // per thread per step; wave 0 adds one (row scales)
   static_assert(BM * 4 <= 1024, "one load of the row scales");
-  static_assert(PERSIST == (NW == 8) && (!PERSIST || STAGES == 2),
-                "the 8-wave tiles are the persistent two-stage ones");
   // uniform over the workgroup: kept in scalar registers
   const int n_live = __builtin_amdgcn_readfirstlane(*g.n_tiles), ntn = g.N / BN;
   int mt, nt;
-  if (!(PERSIST ? work_item_xg<kGroupXcd>(0, n_live, ntn, &mt, &nt)
-                : work_item<kGroupM, false>(0, n_live, ntn, &mt, &nt)))
-    return;
+  if (!work_item_xg<kGroupXcd>(0, n_live, ntn, &mt, &nt)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wid >> 2, wn = wid & 3;
@@ -103,18 +102,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
   __shared__ u32x4 sB[STAGES][BN * 8];
   __shared__ u32x4 sAs[STAGES][BM / 4];
   __shared__ float sBs[8 * (kMaxDim / BK)];
-  // PERSIST GEMM2: the tile's routing coefficients, brought with its first
+  // GEMM2: the tile's routing coefficients, brought with its first
   // stage (they are only needed after the K loop)
-  __shared__ float sW[PERSIST && !SWIGLU ? BM : 1];
+  __shared__ float sW[SWIGLU ? 1 : BM];
   // GEMM2: the tile rows' output rows for direct writes (GemmArgs::ydst);
-  // PERSIST: two buffers, the next tile's loads beside the current epilogue
-  __shared__ int sD[SWIGLU ? 1 : (PERSIST ? 2 : 1)][SWIGLU ? 1 : BM];
+  // two buffers, the next tile's loads beside the current epilogue
+  __shared__ int sD[SWIGLU ? 1 : 2][SWIGLU ? 1 : BM];
 
   auto tile_at = [&](int mt_, int nt_) {
     F8Tile f;
     mt_ = __builtin_amdgcn_readfirstlane(mt_);
     nt_ = __builtin_amdgcn_readfirstlane(nt_);
     f.t = g.tiles[mt_];
+    f.t.rows = __builtin_amdgcn_readfirstlane(f.t.rows);
     f.nt = nt_;
     const uint8_t *blob = blob_of(g.bt, f.t.expert);
     f.Ag = (const char *)(g.A + (size_t)f.t.row0 * K);
@@ -129,10 +129,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
     const int r = seg * 8 + seg_row;
     return (uint32_t)r * K + (uint32_t)(((lane & 7) ^ ((r >> 1) & 7)) * 16);
   };
-  auto stage = [&](const F8Tile &f, int kb, int buf) {
+  // part: only the 8-row A segments that hold rows
+  auto stage = [&](const F8Tile &f, int kb, int buf, bool part = false) {
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
       const int seg = wid * A_LD + i;
+      if (part && seg * 8 >= f.t.rows) break;
       dma16_s(f.Ag + (size_t)kb * BK, lane_off(seg),
               __builtin_amdgcn_readfirstlane(lds_offset(&sA[buf][seg * 64])));
     }
@@ -150,7 +152,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
   // each, by waves 1 and 2 (the rows of a tile lie inside the layout's
   // padded rows)
   auto stage_coef = [&](const F8Tile &f, int db) {
-    if constexpr (PERSIST && !SWIGLU) {
+    if constexpr (!SWIGLU) {
       static_assert(BM * 4 == 1024, "one 1 KB load");
       if (wid == 1)
         dma16_s(g.wrow + f.t.row0, lane * 16, __builtin_amdgcn_readfirstlane(lds_offset(&sW[0])));
@@ -168,14 +170,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s)
     if (s < nkb) stage(cur, s, s % STAGES);
-  int db = 0;  // PERSIST GEMM2: sD buffer of the current tile
+  int db = 0;  // GEMM2: sD buffer of the current tile
   stage_coef(cur, db);
   for (int i = tid; i < nbs; i += 64 * NW) sBs[i] = cur.bs[i];
-  // a PERSIST tile's K loop starts without a wait: its first stage (and the
+  // a tile's K loop starts without a wait: its first stage (and the
   // coefficients) must have landed for every wave here.  The direct loads
   // are invisible to the compiler, so __syncthreads() alone would not wait
   // for them in the waves that load no block scale.
-  if constexpr (PERSIST) wait_vmcnt<0>();
+  wait_vmcnt<0>();
   __syncthreads();
 
   const int r16 = lane & 15, grp = lane >> 4;
@@ -190,33 +192,31 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
     const u32x4 hi = s[row * 8 + ((grp + 4) ^ rsw)];
     return __builtin_bit_cast(i32x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  // stores each wave issues at least in a PERSIST epilogue (FULL staging,
-  // 512 threads): GEMM1 256 x 128 code bytes in 16-byte pieces (4) and one
+  // stores each wave issues at least in an epilogue (512
+  // threads): GEMM1 256 x 128 code bytes in 16-byte pieces (4) and one
   // scale word; GEMM2 two passes of 128 x 512 bytes (8 each; the staging
   // counts its direct float32 rows' extra stores)
   constexpr int S_EPI = SWIGLU ? 4 : 16;
   // block scales per thread (at most 8 or 2 rows of kMaxDim/BK per tile)
-  constexpr int NBSV = PERSIST ? (SWIGLU ? 8 : 2) * (kMaxDim / BK) / (64 * NW) : 1;
+  constexpr int NBSV = (SWIGLU ? 8 : 2) * (kMaxDim / BK) / (64 * NW);
 
   for (int it = 0;; ++it) {
     float wr[8];
-    int ydv = -1;  // non-PERSIST GEMM2: row tid's output row, to sD after the K loop
-    if (!SWIGLU && !PERSIST) {
-      load_row_coef(g, cur.t, wm, lane, wr);
-      if (g.ydst && tid < BM) ydv = g.ydst[(size_t)cur.t.row0 + tid];
-    }
     f32x4 acc[8][4];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
 
-    for (int kb = 0; kb < nkb; ++kb) {
+    // this wave's row fragments that hold rows
+    const int nfr = (cur.t.rows - wm * 128 + 15) >> 4;
+    auto k_step = [&](int kb, auto part_c) {
+      constexpr bool PART = decltype(part_c)::value;
       // this wave's loads of step kb are done when at most the loads of the
-      // steps issued after it are outstanding (a PERSIST tile's first stage
+      // steps issued after it are outstanding (a tile's first stage
       // was waited for before its block scales went to LDS)
       const int later = min(nkb - 1, kb + STAGES - 2) - kb;
-      if (!PERSIST || kb > 0) {
+      if (kb > 0) {
         if (wid == 0)
           wait_stages<PER + 1, STAGES - 2>(later);
         else
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
       }
       // every wave's loads of step kb landed; step kb-1 fully consumed
       __builtin_amdgcn_s_barrier();
-      if (kb + STAGES - 1 < nkb) stage(cur, kb + STAGES - 1, (kb + STAGES - 1) % STAGES);
+      if (kb + STAGES - 1 < nkb) stage(cur, kb + STAGES - 1, (kb + STAGES - 1) % STAGES, PART);
       const int buf = kb % STAGES;
       const float sb0 = sb_row0[kb], sb1 = sb_row1[kb];
       const uint2 sa = ((const uint2 *)&sAs[buf][0])[wm * 64 + grp * 16 + r16];
@@ -237,6 +237,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
       i32x8 a_next = read_op(sA[buf], wm * 128 + r16);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
+        if (PART && i >= nfr) break;  // uniform over the wave
         const i32x8 a = a_next;
         if (i + 1 < 8) a_next = read_op(sA[buf], wm * 128 + (i + 1) * 16 + r16);
         const int sai = (int)(i < 4 ? sa.x : sa.y);
@@ -246,26 +247,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] += p[j] * (j < 2 ? sb0 : sb1);
       }
+    };
+    // GEMM1: a wave whose row fragments are not all in use runs a K loop of
+    // its own that skips them (16 experts of 325 rows, d 7168: 224 -> 215 us; a
+    // test per fragment in the common loop costs full tiles their schedule and 24 more
+    // spilled registers; GEMM2, with its shorter K loop, lost 15 % to the
+    // second loop's registers)
+    if (!SWIGLU || nfr >= 8) {
+      for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::false_type{});
+    } else {
+      for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::true_type{});
     }
 
-    if constexpr (!PERSIST) {
-      // staging: BM x 128 code bytes; y rows of 512 bytes, 64 per 32 KB piece
-      static_assert(sizeof(sA) >= BM * 128, "the h tile fits the A ring");
-      static_assert(sizeof(sB[0]) >= 64 * 512, "y rows fit the ring");
-      if constexpr (!SWIGLU) {
-        // read after the epilogue's first barrier
-        if (tid < BM) sD[0][tid] = ydv;
-      }
-      if constexpr (SWIGLU) {
-        store_h_mx_staged<NW>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[0][0]);
-      } else {
-        uint32_t yb[8][4][2];
-        pack_y_bf16(acc, wr, yb);
-        store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sB[0][0], &sB[1][0],
-                                &sD[0][0]);
-      }
-      return;
-    } else {
+    {
       // GEMM2: the outputs are scaled by the coefficients (in LDS since the
       // tile's first step) and packed to bf16 before the next tile's
       // coefficients overwrite them
@@ -298,9 +292,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
                         sizeof(sB[1]) >= 64 * 512, "staging fits buffer 1");
       int n_st = S_EPI;
       if constexpr (SWIGLU)
-        store_h_mx_staged<NW, true>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
+        store_h_mx_staged<NW>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
       else
-        n_st = store_y_bf16_staged<NW, true>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0],
+        n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0],
                                              &sB[1][0], &sD[db][0]);
       if (!more) return;
       // the next tile's first stage and block scales landed once at most the
@@ -324,20 +318,15 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_fp8(GemmArgs g) {
 }  // namespace
 
 template <bool SWIGLU>
-hipError_t launch_fp8(const GemmArgs &g, int grid_tiles, int align, hipStream_t s) {
+hipError_t launch_fp8(const GemmArgs &g, int grid_tiles, hipStream_t s) {
   if (g.N % 256 || g.K % 128 || g.K > kMaxDim || g.s_ld % 256) return hipErrorInvalidValue;
   const int grid = balanced_grid(grid_tiles, kGroupM, g.N / 256);
-  if (align == kFp8TileM)
-    hipLaunchKernelGGL((k_gemm_fp8<4, 3, SWIGLU, false>), dim3(grid), dim3(256), 0, s, g);
-  else if (align == kFp8LargeTileM)
-    hipLaunchKernelGGL((k_gemm_fp8<8, 2, SWIGLU, true>), dim3(std::min(grid, persistent_grid())),
-                       dim3(512), 0, s, g);
-  else
-    return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_gemm_fp8<SWIGLU>), dim3(std::min(grid, persistent_grid())), dim3(512), 0,
+                     s, g);
   return hipGetLastError();
 }
 
-template hipError_t launch_fp8<true>(const GemmArgs &, int, int, hipStream_t);
-template hipError_t launch_fp8<false>(const GemmArgs &, int, int, hipStream_t);
+template hipError_t launch_fp8<true>(const GemmArgs &, int, hipStream_t);
+template hipError_t launch_fp8<false>(const GemmArgs &, int, hipStream_t);
 
 }  // namespace cep

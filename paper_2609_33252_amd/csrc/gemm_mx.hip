@@ -18,6 +18,7 @@
 #include "gemm_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace cep {
 namespace {
@@ -39,12 +40,12 @@ __device__ inline f32x4 mx_mfma(const i32x8 &w, const i32x8 &x, const f32x4 &c, 
   }
 }
 
-// BM x 256 output tile, K step 128 (four scale blocks).  NW waves: four
-// column groups of 64 x (NW/4) row groups of 128; each wave owns 128 rows x
-// 64 columns = 8 x 4 16x16 fragments.  A stage holds BM x 128 e4m3 codes,
-// 256 x 64 bytes of packed e2m1 weights, the BM x 4 row scales and the 256 x
-// 4 weight scales, all brought by direct global->LDS loads issued STAGES-1
-// steps ahead.  The scale layouts (mx_row_scale_offset,
+// 256 x 256 output tile, K step 128 (four scale blocks), 8 waves: four column
+// groups of 64 x two row groups of 128; each wave owns 128 rows x 64 columns =
+// 8 x 4 16x16 fragments.  A stage holds 256 x 128 e4m3
+// codes, 256 x 64 bytes of packed e2m1 weights, the 256 x 4 row scales and the
+// 256 x 4 weight scales, all brought by direct global->LDS loads issued one
+// step ahead.  The scale layouts (mx_row_scale_offset,
 // mx_weight_scale_offset) give each lane its eight row scales as one 8-byte
 // word and its four column scales as one word; the MFMA's byte select picks
 // the fragment's byte.
@@ -57,136 +58,10 @@ __device__ inline f32x4 mx_mfma(const i32x8 &w, const i32x8 &x, const f32x4 &c, 
 // with SQ_LDS_BANK_CONFLICT); with these swizzles each such group reads
 // sixteen distinct 16-byte slots of 256 bytes in both operand reads.
 //
-// Epilogues: store_h_mx_staged (GEMM1) and store_y_bf16 (GEMM2).  The
-// 256-row tiles run as the persistent 8-wave kernel below (same stage, LDS
-// layout and MFMA order, so both tile heights give bitwise equal outputs).
+// Epilogues: store_h_mx_staged (GEMM1) and store_y_bf16_staged (GEMM2).
 __device__ inline int bsw_of(int r) { return (r & 1) | ((r >> 1) & 2); }
 
-
-template <int NW, int STAGES, bool SWIGLU, int OCC = 1>
-__global__ __launch_bounds__(64 * NW, OCC) void k_gemm_mx(GemmArgs g) {
-  constexpr int BM = 128 * NW / 4, BN = 256, BK = 128;
-  constexpr int A_SEG = BM * BK / 1024, B_SEG = BN * (BK / 2) / 1024;
-  constexpr int A_LD = A_SEG / NW, B_LD = B_SEG / NW;  // 1 KB loads per wave per step
-  constexpr int PER = A_LD + B_LD;  // waves 0 and 1 add one each (row / weight scales)
-  static_assert(A_SEG % NW == 0 && B_SEG % NW == 0, "loads split evenly over the waves");
-  static_assert(BM * 4 <= 1024, "one load of the row scales");
-  int mt, nt;
-  if (!balanced_tile<kGroupM>(*g.n_tiles, g.N / BN, &mt, &nt)) return;
-  const Tile t = g.tiles[mt];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wid >> 2, wn = wid & 3;
-  const int K = g.K, nkb = K / BK, KB = K / 2;  // KB: bytes of one packed weight row
-  const uint8_t *blob = blob_of(g.bt, t.expert);
-  const char *Ag = (const char *)(g.A + (size_t)t.row0 * K);
-  const char *Bg = (const char *)(blob + g.b_off);  // mx_block_index layout
-  // row scales of K step kb: 512 bytes per 128-row group, groups contiguous
-  const char *Asg = (const char *)g.As + (size_t)(t.row0 >> 7) * 512;
-  const size_t as_step = (size_t)(g.s_ld >> 7) * 512;
-  const char *Bsg = (const char *)(blob + g.bs_off) + (size_t)nt * nkb * 1024;
-
-  __shared__ u32x4 sA[STAGES][BM * 8];
-  __shared__ u32x4 sB[STAGES][BN * 4];
-  __shared__ u32x4 sAs[STAGES][BM / 4];
-  __shared__ u32x4 sBs[STAGES][64];
-
-  const int a_row = lane >> 3, b_row = lane >> 2;
-#define CEP_MX_STAGE(kb)                                                            \
-  {                                                                                 \
-    const int buf_ = (kb) % STAGES;                                                 \
-    _Pragma("unroll") for (int i = 0; i < A_LD; ++i) {                              \
-      const int seg = wid * A_LD + i, r = seg * 8 + a_row;                          \
-      dma16(Ag + (size_t)(kb) * BK + (size_t)r * K + (((lane & 7) ^ ((r >> 1) & 7)) * 16), \
-            __builtin_amdgcn_readfirstlane(lds_offset(&sA[buf_][seg * 64])));       \
-    }                                                                               \
-    _Pragma("unroll") for (int i = 0; i < B_LD; ++i) {                              \
-      const int seg = wid * B_LD + i, r = seg * 16 + b_row;                         \
-      dma16(Bg + mx_block_index(nt * BN + r, (kb) * (BK / 2) + ((lane & 3) ^ bsw_of(r)) * 16, KB), \
-            __builtin_amdgcn_readfirstlane(lds_offset(&sB[buf_][seg * 64])));       \
-    }                                                                               \
-    if (wid == 0 && lane < BM / 4)                                                  \
-      dma16(Asg + (size_t)(kb) * as_step + lane * 16,                               \
-            __builtin_amdgcn_readfirstlane(lds_offset(&sAs[buf_][0])));             \
-    if (wid == 1)                                                                   \
-      dma16(Bsg + (size_t)(kb) * 1024 + lane * 16,                                  \
-            __builtin_amdgcn_readfirstlane(lds_offset(&sBs[buf_][0])));             \
-  }
-
-  f32x4 acc[8][4];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
-
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nkb) CEP_MX_STAGE(s);
-
-  float wr[8];
-  int yd[8];  // GEMM2: output rows of the lane's rows (GemmArgs::ydst)
-  if constexpr (!SWIGLU) {
-    load_row_coef(g, t, wm, lane, wr);
-    load_row_dst(g, t, wm, lane, yd);
-  }
-  const int r16 = lane & 15, grp = lane >> 4;
-  const int asw = (r16 >> 1) & 7;  // A swizzle of every row this lane reads
-  const int bsw = bsw_of(r16);     // B swizzle of every row this lane reads
-  for (int kb = 0; kb < nkb; ++kb) {
-    const int later = min(nkb - 1, kb + STAGES - 2) - kb;
-    if (wid < 2)
-      wait_stages<PER + 1, STAGES - 2>(later);
-    else
-      wait_stages<PER, STAGES - 2>(later);
-    // every wave's loads of step kb landed; step kb-1 fully consumed
-    __builtin_amdgcn_s_barrier();
-    if (kb + STAGES - 1 < nkb) CEP_MX_STAGE(kb + STAGES - 1);
-    const int cur = kb % STAGES;
-    const uint32_t sb = ((const uint32_t *)&sBs[cur][0])[(wn * 4 + grp) * 16 + r16];
-    const uint2 sa = ((const uint2 *)&sAs[cur][0])[wm * 64 + grp * 16 + r16];
-
-    i32x8 b[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = wn * 64 + j * 16 + r16;
-      const u32x4 v = sB[cur][row * 4 + (grp ^ bsw)];
-      b[j] = __builtin_bit_cast(i32x8, __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1));
-    }
-    // A fragments one row group ahead: the reads of group i+1 are issued
-    // before the MFMAs of group i, so LDS latency hides behind them
-    auto read_a = [&](int i) {
-      const int row = wm * 128 + i * 16 + r16;
-      const u32x4 lo = sA[cur][row * 8 + (grp ^ asw)];
-      const u32x4 hi = sA[cur][row * 8 + ((grp + 4) ^ asw)];
-      return __builtin_bit_cast(i32x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-    i32x8 a_next = read_a(0);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const i32x8 a = a_next;
-      if (i + 1 < 8) a_next = read_a(i + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      const int sai = (int)(i < 4 ? sa.x : sa.y);
-      acc[i][0] = mx_mfma<0>(b[0], a, acc[i][0], i & 3, sai, (int)sb);
-      acc[i][1] = mx_mfma<1>(b[1], a, acc[i][1], i & 3, sai, (int)sb);
-      acc[i][2] = mx_mfma<2>(b[2], a, acc[i][2], i & 3, sai, (int)sb);
-      acc[i][3] = mx_mfma<3>(b[3], a, acc[i][3], i & 3, sai, (int)sb);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#undef CEP_MX_STAGE
-
-  // GEMM1 stages BM x 128 code bytes through the A ring
-  static_assert(sizeof(sA) >= BM * 128, "the h tile fits the A ring");
-  if constexpr (SWIGLU) {
-    store_h_mx_staged<NW>(acc, g, t, nt, wm, wn, lane, tid, &sA[0][0]);
-  } else {
-    store_y_bf16(acc, wr, yd, g, t, nt, wm, wn, lane);
-  }
-}
-
-
-// Persistent 8-wave tiles, as the e4m3 GEMMs': one workgroup per CU walks
+// Persistent, as the e4m3 GEMMs: one workgroup per CU walks
 // its XCD's share of the tile order (work_item_xg).  After a tile's K loop
 // it issues the next tile's first stage into ring buffer 0 (and, for
 // GEMM2, the next tile's routing coefficients and output rows into LDS),
@@ -229,6 +104,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
     mt_ = __builtin_amdgcn_readfirstlane(mt_);
     nt_ = __builtin_amdgcn_readfirstlane(nt_);
     f.t = g.tiles[mt_];
+    f.t.rows = __builtin_amdgcn_readfirstlane(f.t.rows);
     f.nt = nt_;
     const uint8_t *blob = blob_of(g.bt, f.t.expert);
     f.Ag = (const char *)(g.A + (size_t)f.t.row0 * K);
@@ -240,10 +116,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
     return f;
   };
   const int a_row = lane >> 3, b_row = lane >> 2;
-  auto stage = [&](const MxTile &f, int kb, int buf) {
+  // part: only the 8-row A segments that hold rows
+  auto stage = [&](const MxTile &f, int kb, int buf, bool part = false) {
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
       const int seg = wid * A_LD + i, r = seg * 8 + a_row;
+      if (part && seg * 8 >= f.t.rows) break;
       dma16(f.Ag + (size_t)kb * BK + (size_t)r * K + (((lane & 7) ^ ((r >> 1) & 7)) * 16),
             __builtin_amdgcn_readfirstlane(lds_offset(&sA[buf][seg * 64])));
     }
@@ -298,13 +176,16 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
-    for (int kb = 0; kb < nkb; ++kb) {
+    // this wave's row fragments that hold rows
+    const int nfr = (cur.t.rows - wm * 128 + 15) >> 4;
+    auto k_step = [&](int kb, auto part_c) {
+      constexpr bool PART = decltype(part_c)::value;
       // this wave's loads of step kb are its only ones outstanding (a
       // tile's first stage was waited for before its K loop)
       if (kb > 0) wait_vmcnt<0>();
       // every wave's loads of step kb landed; step kb-1 fully consumed
       __builtin_amdgcn_s_barrier();
-      if (kb + 1 < nkb) stage(cur, kb + 1, (kb + 1) & 1);
+      if (kb + 1 < nkb) stage(cur, kb + 1, (kb + 1) & 1, PART);
       const int buf = kb & 1;
       const uint32_t sb = ((const uint32_t *)&sBs[buf][0])[(wn * 4 + grp) * 16 + r16];
       const uint2 sa = ((const uint2 *)&sAs[buf][0])[wm * 64 + grp * 16 + r16];
@@ -324,6 +205,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
       i32x8 a_next = read_a(0);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
+        if (PART && i >= nfr) break;  // uniform over the wave
         const i32x8 a = a_next;
         if (i + 1 < 8) a_next = read_a(i + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -334,6 +216,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
         acc[i][3] = mx_mfma<3>(b[3], a, acc[i][3], i & 3, sai, (int)sb);
         __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    // GEMM1: a wave whose row fragments are not all in use runs a K loop of
+    // its own that skips them (16 experts of 316 to 516 rows, d 7168: 172 ->
+    // 164 and 252 -> 237 us; GEMM2 did not gain)
+    if (!SWIGLU || nfr >= 8) {
+      for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::false_type{});
+    } else {
+      for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::true_type{});
     }
     // GEMM2: outputs scaled by the coefficients and packed to bf16 before
     // the next tile's coefficients overwrite them
@@ -361,9 +251,9 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
                   "staging fits buffer 1 and sY");
     int n_st = S_EPI;
     if constexpr (SWIGLU)
-      store_h_mx_staged<NW, true>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
+      store_h_mx_staged<NW>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
     else
-      n_st = store_y_bf16_staged<NW, true>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0],
+      n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0],
                                            &sY[0], &sD[db][0]);
     if (!more) return;
     // the next tile's first stage (and coefficients) landed once at most the
@@ -382,24 +272,15 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
 }  // namespace
 
 template <bool SWIGLU>
-hipError_t launch_mx(const GemmArgs &g, int grid_tiles, int align, hipStream_t s) {
+hipError_t launch_mx(const GemmArgs &g, int grid_tiles, hipStream_t s) {
   if (g.N % 256 || g.K % 128 || g.K > kMaxDim || g.s_ld % 256) return hipErrorInvalidValue;
   const int grid = balanced_grid(grid_tiles, kGroupM, g.N / 256);
-  // 128-row tiles: two stages (68 KB of LDS) so that two workgroups share a
-  // CU -- one wave per SIMD cannot hide the load latency of a 4-wave tile,
-  // two can (25-40 % faster than four stages at one workgroup per CU on
-  // batches of 128-256 rows per expert)
-  if (align == kFp8TileM)
-    hipLaunchKernelGGL((k_gemm_mx<4, 2, SWIGLU, 2>), dim3(grid), dim3(256), 0, s, g);
-  else if (align == kFp8LargeTileM)
-    hipLaunchKernelGGL((k_gemm_mx_persist<SWIGLU>), dim3(std::min(grid, persistent_grid())),
-                       dim3(512), 0, s, g);
-  else
-    return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_gemm_mx_persist<SWIGLU>), dim3(std::min(grid, persistent_grid())),
+                     dim3(512), 0, s, g);
   return hipGetLastError();
 }
 
-template hipError_t launch_mx<true>(const GemmArgs &, int, int, hipStream_t);
-template hipError_t launch_mx<false>(const GemmArgs &, int, int, hipStream_t);
+template hipError_t launch_mx<true>(const GemmArgs &, int, hipStream_t);
+template hipError_t launch_mx<false>(const GemmArgs &, int, hipStream_t);
 
 }  // namespace cep

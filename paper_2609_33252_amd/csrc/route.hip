@@ -121,9 +121,7 @@ struct PlanArgs {
   int E, align, expected_pairs, max_mpad, max_tiles;
   uint64_t fetched_mask;
   int split_cu, n_tiles_n;
-  // second list of each kind: kListVar each expert's 128-row tiles,
-  // kListSorted the 64-row tiles ordered by rows, most first; kListNone none
-  int list2;
+  int list2;  // second list of each kind (batch_list2)
   uint32_t *err;
 };
 
@@ -189,6 +187,7 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
     const int n2 = rem                       ? tiles_of(r, kBf16SmallTileM)
                    : a.list2 == kListVar     ? tiles_of(c, kBf16VarTileM)
                    : a.list2 == kListSorted  ? nall
+                   : a.list2 == kListHalf    ? tiles_of(c, 64)
                                              : 0;
     const int so = wave_scan(c), sp = wave_scan(nall << ash);
     int s1[2], s2[2], sf[2];
@@ -278,6 +277,13 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
         const int span = rows > kBf16VarTileM / 2 ? kBf16VarTileM : kBf16VarTileM / 2;
         if (ti >= a.max_tiles || row0 + span > a.max_mpad) break;
         list2[ti] = Tile{x, row0, rows, 0};
+      }
+    }
+    if (a.list2 == kListHalf) {
+      for (int q = lane; q * 64 < c; q += 64) {
+        const int ti = rt0 + q, row0 = pad + q * 64;
+        if (ti >= a.max_tiles || row0 + 64 > a.max_mpad) break;
+        list2[ti] = Tile{x, row0, min(64, c - q * 64), 0};
       }
     }
     if (rem) {

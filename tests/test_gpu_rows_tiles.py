@@ -1,0 +1,58 @@
+"""Few-row tiles of the e4m3 and MXFP4 GEMMs at their edges: experts whose row
+counts sit at the edges of the 8-row load segments, the 16-row fragments and
+the 64- and 128-row tiles, every row against the oracle (the bounds of
+_util.check).  The K loops have one, two, three and six steps."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_33252_amd import cep, harness, workload as W
+
+from . import _util as U
+
+pytestmark = pytest.mark.gpu
+
+# rows per expert: the 64-row tiles (fewer than 64 pairs per expert on
+# average) and the 128-row tiles
+COUNTS = {"rows64": [1, 8, 9, 16, 17, 0, 64, 65, 128, 129, 63, 7],
+          "rows128": [127, 128, 129, 1, 112, 113, 0, 256, 257, 64, 15, 240]}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cep.lib()
+
+
+@pytest.mark.parametrize("tiles", list(COUNTS))
+@pytest.mark.parametrize("shape", [(768, 384), (256, 128)], ids=["d768", "d256"])
+@pytest.mark.parametrize("name", ["fp8_fetch_d6144", "mxfp4_dsv4flash_d4096"])
+def test_row_counts_at_tile_edges(name, shape, tiles):
+    cnt = COUNTS[tiles]
+    E, (d, I) = len(cnt), shape
+    print(f"case {name} d={d} I={I} {tiles}", flush=True)
+    # every expert local, so every token is delivered; then one local slot per
+    # token up to the counts, and a second one (of the next expert) for some
+    wl = W.generate(name, 31, d=d, I=I, E=E, Eg=E, k=2, R=1, T=2048, cpr=1, fetch_frac=0.0)
+    ids = np.full((2048, 2), -1, np.int32)
+    own = np.repeat(np.arange(E, dtype=np.int32), cnt)
+    order = np.random.default_rng(5).permutation(len(own))
+    half = len(own) // 2
+    ids[:len(own) - half, 0] = own[order[:len(own) - half]]
+    rest = own[order[len(own) - half:]]
+    both = rest != ids[:half, 0]  # a token's slots name distinct experts
+    ids[:half, 1][both] = rest[both]
+    ids[1024:1024 + int((~both).sum()), 0] = rest[~both]
+    wl.topk_local = ids.reshape(1, 2048, 2)
+    assert wl.n_pairs == sum(cnt)
+    assert (wl.n_pairs < 64 * E) == (tiles == "rows64")
+    run = harness.Runner(wl, n_streams=1, record_routing=True, use_fetch=False)
+    run.run(policy=cep.CEP_WAIT_ALL)
+    torch.cuda.synchronize()
+    cep.cep_get_status(run.ctx)
+    m = cep.cep_get_batch_routing(run.ctx, 0, E, 2)
+    got = run.out.cpu().numpy()
+    run.close()
+    assert m["align"] == 128 and list(m["cnt"]) == cnt
+    U.check(wl, got)
