@@ -252,10 +252,17 @@ hipError_t launch_ingest(const Arena &a, const IngestGroup &grp, int k, int E, i
 // when its makespan estimate for split_cu compute units and GEMM1's
 // n_tiles_n 256-wide column tiles improves.  list2: the scan's second list of
 // each kind (batch_list2).
-hipError_t launch_route(const Arena &a, const Scratch &sc, int row0, int n_rows, int k, int E,
-                        int align, int expected_pairs, int max_mpad, int max_tiles,
-                        uint64_t fetched_mask, int x_dtype, int wk, int d, int split_cu,
-                        int n_tiles_n, int list2, uint32_t *err, hipStream_t s);
+// stage (may be null; stage_in_route must hold): the routing launch stages
+// the batch's chunks itself, no launch_ingest before it.
+hipError_t launch_route(const Arena &a, const Scratch &sc, const IngestGroup *stage, int t_max,
+                        size_t x_row_bytes, int row0, int n_rows, int k, int E, int align,
+                        int expected_pairs, int max_mpad, int max_tiles, uint64_t fetched_mask,
+                        int x_dtype, int wk, int d, int split_cu, int n_tiles_n, int list2,
+                        uint32_t *err, hipStream_t s);
+// The chunks of grp are exactly a batch's rows, few enough for the one-block
+// routing kernel to stage them.
+constexpr int kStageChunks = 8;
+bool stage_in_route(const IngestGroup &grp, int row0, int n_rows, int k);
 // y_f32: the grouped outputs are float32 (bf16 weights), else bf16.
 // skip_solo: the batch's GEMM2 wrote the output rows of tokens with one
 // local pair (gemm2_writes_solo); the combine leaves them alone.

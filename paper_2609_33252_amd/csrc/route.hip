@@ -305,20 +305,81 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
 // [w*span, (w+1)*span) and walks them in order, so a pair's grouped row is
 // its expert's first row + the pairs of that expert in lower waves + those
 // earlier in its own wave: the same stable order as the multi-block path.
+//
+// STAGE: the batch's chunks are staged here too (k_ingest's work for up to
+// kStageChunks chunks, all of the batch's rows): ids, coefficients and token
+// slots come straight from the chunks into LDS in one memory latency, and the
+// arena gets only what later kernels read (output row, input row pointer,
+// single-pair row).  One launch and one round trip through memory less.  With
+// the direct pack below the route phase of a 64-token chunk (e4m3, d 7168, 16
+// experts) takes 18 us where staging, routing, pack and scale layout took 41.
 constexpr int kFusedWaves = 16;
 
+struct StageArgs {
+  IngestChunk c[kStageChunks];
+  int n, t_max;
+  size_t x_row_bytes;
+};
+
+template <bool STAGE>
 __global__ __launch_bounds__(64 * kFusedWaves) void k_route_fused(Arena a, Scratch sc, int row0,
-                                                                  int n_flat, int k,
-                                                                  PlanArgs pa) {
+                                                                  int n_flat, int k, PlanArgs pa,
+                                                                  StageArgs st) {
   __shared__ int s_ids[kFusedRoutePairs];
+  __shared__ float s_w[STAGE ? kFusedRoutePairs : 1];
+  __shared__ int s_solo[STAGE ? kFusedRoutePairs : 1];  // per row: output row, then solo
   __shared__ int wcnt[kFusedWaves][kMaxExperts];  // counts, then running rows
   __shared__ PlanLds L;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, E = pa.E;
   constexpr int NT = 64 * kFusedWaves;
-  const int32_t *ids = a.ids + (size_t)row0 * k;
   for (int i = tid; i < kFusedWaves * kMaxExperts; i += NT) (&wcnt[0][0])[i] = 0;
+  if constexpr (STAGE) {
+    const int n_rows = n_flat / k;
+    // the chunk of a row of the batch: the last one starting at or before it
+    auto chunk_of = [&](int r) {
+      int x = 0;
+#pragma unroll
+      for (int q = 1; q < kStageChunks; ++q)
+        if (q < st.n && st.c[q].row0 - row0 <= r) x = q;
+      return x;
+    };
+    uint32_t bad = 0;
+    for (int i = tid; i < n_flat; i += NT) {
+      const IngestChunk &c = st.c[chunk_of(i / k)];
+      const int f = i - (c.row0 - row0) * k;
+      s_ids[i] = c.topk_id[f];
+      s_w[i] = c.topk_w[f];
+    }
+    for (int r = tid; r < n_rows; r += NT) {
+      const IngestChunk &c = st.c[chunk_of(r)];
+      const int q = r - (c.row0 - row0), t = c.token_idx[q];
+      s_solo[r] = t >= 0 && t < st.t_max ? c.replica * st.t_max + t : -1;
+      a.xrow[row0 + r] = (const char *)c.x + (size_t)q * st.x_row_bytes;
+    }
+    __syncthreads();
+    for (int r = tid; r < n_rows; r += NT) {
+      const int dst = s_solo[r];
+      if (dst < 0) bad |= kErrBadToken;
+      int n_local = 0;
+      for (int q = 0; q < k; ++q) {
+        const int id = s_ids[r * k + q];
+        if (id < -1 || id >= E) bad |= kErrBadId;
+        if (id < 0 || id >= E || dst < 0)
+          s_ids[r * k + q] = -1;
+        else
+          ++n_local;
+      }
+      const int solo = n_local == 1 ? dst : -1;
+      s_solo[r] = solo;
+      a.dst[row0 + r] = dst;
+      a.solo[row0 + r] = solo;
+    }
+    if (bad) atomicOr(pa.err, bad);
+  } else {
+    const int32_t *ids = a.ids + (size_t)row0 * k;
 #pragma unroll 8
-  for (int i = tid; i < n_flat; i += NT) s_ids[i] = ids[i];
+    for (int i = tid; i < n_flat; i += NT) s_ids[i] = ids[i];
+  }
   __syncthreads();
   const int span = (n_flat + 64 * kFusedWaves - 1) / (64 * kFusedWaves) * 64;
   const int p0 = min(wid * span, n_flat), p1 = min(p0 + span, n_flat);
@@ -360,8 +421,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_route_fused(Arena a, Scrat
       sc.pos_of[p] = pos;
       if (pos >= 0) {
         sc.perm[pos] = p;
-        sc.wrow[pos] = a.w[(size_t)row0 * k + p];  // the row's routing coefficient
-        sc.ydst[pos] = a.solo[row0 + p / k];
+        // the row's routing coefficient
+        sc.wrow[pos] = STAGE ? s_w[STAGE ? p : 0] : a.w[(size_t)row0 * k + p];
+        sc.ydst[pos] = STAGE ? s_solo[STAGE ? p / k : 0] : a.solo[row0 + p / k];
       }
     }
   }
@@ -484,8 +546,10 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_scan_scatter(Arena a, S
 // as they are: their outputs are never stored.  bf16 rows are not packed:
 // the bf16 GEMM1 gathers them through the permutation.
 constexpr int kPackRows = 8;
-
-constexpr int kQuantPass = 8;  // 512-channel groups loaded per pass of a quantised row
+// pairs up to which the MXFP8 pack stores its scale bytes one by one (route
+// phase of 16 experts, d 7168: 20 against 32 us with 256 pairs, 48 against 51
+// with 4 K, 100 against 102 with 16 K, 168 against 161 with 33 K)
+constexpr int kPackDirectPairs = 1 << 14;
 
 __device__ inline void bf16x8_to_f32(const uint4 &u, float v[8]) {
   const uint32_t w[4] = {u.x, u.y, u.z, u.w};
@@ -546,13 +610,16 @@ __global__ __launch_bounds__(256) void k_pack_rows(Arena a, Scratch sc, int row0
   }
 }
 
-// bf16 -> MXFP8 rows (e4m3 and MXFP4 weights), one wave per batch row: the
-// row is read and quantised once and its codes and scales written to the
-// grouped row of each of its local slots (a token averages 1.3 local slots
-// on the skewed workloads, so reading per token rather than per pair saves a
-// quarter of the reads).  A pass first loads up to kQuantPass 512-channel
-// groups (eight channels per lane), then quantises them, so that many loads
-// are in flight per wave.
+// bf16 -> MXFP8 rows (e4m3 and MXFP4 weights): the row is read and quantised
+// once and its codes and scales written to the grouped row of each of its
+// local slots (a token averages 1.3 local slots on the skewed workloads, so
+// reading per token rather than per pair saves a quarter of the reads).  A
+// wave takes NG 512-channel groups (eight channels per lane) of one row,
+// blockIdx.y naming the part of the row, and first loads all of them.  Bound
+// by HBM with many rows (NG 8), by latency with few (DIRECT, NG 2: more waves
+// a row, and the scale bytes go straight to the GEMM's layout, which saves
+// k_scale_layout).
+template <int NG, bool DIRECT>
 __global__ __launch_bounds__(256) void k_pack_tokens(Arena a, Scratch sc, int row0, int n_rows,
                                                      int k, int d) {
   const int lane = threadIdx.x & 63;
@@ -560,30 +627,30 @@ __global__ __launch_bounds__(256) void k_pack_tokens(Arena a, Scratch sc, int ro
   if (i >= n_rows) return;  // uniform over the wave
   static_assert(kMaxTopK <= 64, "a row's slots fit one wave");
   const int ps = lane < k ? sc.pos_of[(size_t)i * k + lane] : -1;
+  const uint4 *s4 = (const uint4 *)a.xrow[row0 + i];
   const uint64_t valid = __ballot(ps >= 0);
   if (valid == 0) return;
-  const uint4 *s4 = (const uint4 *)a.xrow[row0 + i];
-  uint8_t *xs_rows = sc.xs_rows;
-  for (int p0 = 0; p0 < d; p0 += 512 * kQuantPass) {
-    uint4 in[kQuantPass];
+  const int p0 = blockIdx.y * 512 * NG;
+  uint4 in[NG];
 #pragma unroll
-    for (int u = 0; u < kQuantPass; ++u) {
-      const int c = p0 + u * 512 + lane * 8;
-      in[u] = c < d ? s4[c / 8] : make_uint4(0u, 0u, 0u, 0u);
-    }
+  for (int u = 0; u < NG; ++u) {
+    const int c = p0 + u * 512 + lane * 8;
+    in[u] = c < d ? s4[c / 8] : make_uint4(0u, 0u, 0u, 0u);
+  }
 #pragma unroll
-    for (int u = 0; u < kQuantPass; ++u) {
-      if (p0 + u * 512 >= d) break;  // uniform over the wave
-      const int c = p0 + u * 512 + lane * 8;
-      int code;
-      const uint2 q = quant_mx8(in[u], &code);
-      if (c >= d) continue;
-      for (uint64_t m = valid; m; m &= m - 1) {
-        const int pos = __shfl(ps, __builtin_ctzll(m));
-        *(uint2 *)((uint8_t *)sc.xg + (size_t)pos * d + c) = q;
-        // the wave's 16 scale bytes of this pass are contiguous here
-        if ((lane & 3) == 0) xs_rows[(size_t)pos * sc.xs_pitch + c / kMxBlock] = (uint8_t)code;
-      }
+  for (int u = 0; u < NG; ++u) {
+    if (p0 + u * 512 >= d) break;  // uniform over the wave
+    const int c = p0 + u * 512 + lane * 8;
+    int code;
+    const uint2 q = quant_mx8(in[u], &code);
+    if (c >= d) continue;
+    for (uint64_t m = valid; m; m &= m - 1) {
+      const int pos = __shfl(ps, __builtin_ctzll(m));
+      *(uint2 *)((uint8_t *)sc.xg + (size_t)pos * d + c) = q;
+      // DIRECT: 16 runs of the layout; else the 16 bytes are contiguous
+      if ((lane & 3) == 0)
+        *(DIRECT ? (uint8_t *)sc.xs + mx_row_scale_offset(pos, c / kMxBlock, sc.s_ld)
+                 : sc.xs_rows + (size_t)pos * sc.xs_pitch + c / kMxBlock) = (uint8_t)code;
     }
   }
 }
@@ -868,19 +935,42 @@ hipError_t launch_ingest(const Arena &a, const IngestGroup &grp, int k, int E, i
   return hipGetLastError();
 }
 
-hipError_t launch_route(const Arena &a, const Scratch &sc, int row0, int n_rows, int k, int E,
-                        int align, int expected_pairs, int max_mpad, int max_tiles,
-                        uint64_t fetched_mask, int x_dtype, int wk, int d, int split_cu,
-                        int n_tiles_n, int list2, uint32_t *err, hipStream_t s) {
+bool stage_in_route(const IngestGroup &grp, int row0, int n_rows, int k) {
+  if (grp.n < 1 || grp.n > kStageChunks || (long long)n_rows * k > kFusedRoutePairs) return false;
+  int r = row0;
+  for (int i = 0; i < grp.n; ++i) {
+    if (grp.c[i].row0 != r) return false;
+    r += grp.c[i].n_rows;
+  }
+  return r == row0 + n_rows;
+}
+
+hipError_t launch_route(const Arena &a, const Scratch &sc, const IngestGroup *stage, int t_max,
+                        size_t x_row_bytes, int row0, int n_rows, int k, int E, int align,
+                        int expected_pairs, int max_mpad, int max_tiles, uint64_t fetched_mask,
+                        int x_dtype, int wk, int d, int split_cu, int n_tiles_n, int list2,
+                        uint32_t *err, hipStream_t s) {
   const int n_flat = n_rows * k;
   const int nb = (n_flat + kRoutePairs - 1) / kRoutePairs;
   if (nb == 0) return hipSuccess;
   const PlanArgs pa{E, align, expected_pairs, max_mpad, max_tiles, fetched_mask, split_cu,
                     n_tiles_n, list2, err};
   if (n_flat <= kFusedRoutePairs) {
-    hipLaunchKernelGGL(k_route_fused, dim3(1), dim3(64 * kFusedWaves), 0, s, a, sc, row0,
-                       n_flat, k, pa);
+    StageArgs st{};
+    if (stage) {
+      if (!stage_in_route(*stage, row0, n_rows, k)) return hipErrorInvalidValue;
+      std::copy(stage->c, stage->c + stage->n, st.c);
+      st.n = stage->n;
+      st.t_max = t_max;
+      st.x_row_bytes = x_row_bytes;
+      hipLaunchKernelGGL(k_route_fused<true>, dim3(1), dim3(64 * kFusedWaves), 0, s, a, sc, row0,
+                         n_flat, k, pa, st);
+    } else {
+      hipLaunchKernelGGL(k_route_fused<false>, dim3(1), dim3(64 * kFusedWaves), 0, s, a, sc, row0,
+                         n_flat, k, pa, st);
+    }
   } else {
+    if (stage) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_route_count, dim3(nb), dim3(kRouteThreads), 0, s,
                        a.ids + (size_t)row0 * k, n_flat, E, sc.blk_cnt);
     hipLaunchKernelGGL(k_route_scan_scatter, dim3(nb + 1), dim3(kRouteThreads), 0, s, a, sc,
@@ -890,8 +980,14 @@ hipError_t launch_route(const Arena &a, const Scratch &sc, int row0, int n_rows,
   const long long bound = ((long long)(expected_pairs + align - 1) / align + E) * align;
   const int n_pad = (int)std::min<long long>(bound, max_mpad);
   if (wk == kWMx || wk == kWFp8) {
-    hipLaunchKernelGGL(k_pack_tokens, dim3((n_rows + 3) / 4), dim3(256), 0, s, a, sc, row0, n_rows,
-                       k, d);
+    const dim3 rows((n_rows + 3) / 4);
+    if (expected_pairs <= kPackDirectPairs) {
+      hipLaunchKernelGGL((k_pack_tokens<2, true>), dim3(rows.x, (d + 1023) / 1024), dim3(256), 0,
+                         s, a, sc, row0, n_rows, k, d);
+      return hipGetLastError();
+    }
+    hipLaunchKernelGGL((k_pack_tokens<8, false>), dim3(rows.x, (d + 4095) / 4096), dim3(256), 0, s,
+                       a, sc, row0, n_rows, k, d);
     const int nb = d / kMxBlock;
     hipLaunchKernelGGL(k_scale_layout, dim3((n_pad + 127) / 128, (nb + kScaleCols - 1) / kScaleCols),
                        dim3(256), 0, s, sc, nb);

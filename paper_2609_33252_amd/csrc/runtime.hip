@@ -217,20 +217,31 @@ void free_batch_records(cep_ctx *c) {
   c->batches.clear();
 }
 
+// The chunks with rows of [from, upto) into g, at most kIngestGroup of them;
+// returns the first chunk not taken.
+int64_t stage_group(const cep_ctx *c, int64_t from, int64_t upto, IngestGroup *g) {
+  g->n = 0;
+  for (; g->n < kIngestGroup && from < upto; ++from) {
+    const ChunkRec &ch = c->chunks[from];
+    if (ch.n_rows > 0)
+      g->c[g->n++] = IngestChunk{ch.token_idx, ch.x, ch.topk_id, ch.topk_w, ch.row0, ch.n_rows,
+                                 ch.replica};
+  }
+  return from;
+}
+
+size_t x_row_bytes(const cep_config &cfg) {
+  return (size_t)cfg.d_model * (cfg.x_dtype == CEP_F32 ? 4 : 2);
+}
+
 // Stages the metadata of chunks [c->staged, upto) into the arena on stream s
 // (one launch per group of chunks), after their arrival waits.
 int stage_chunks(cep_ctx *c, int64_t upto, hipStream_t s) {
-  const size_t xrb = (size_t)c->cfg.d_model * (c->cfg.x_dtype == CEP_F32 ? 4 : 2);
   while (c->staged < upto) {
-    IngestGroup g{};
-    while (g.n < kIngestGroup && c->staged < upto) {
-      const ChunkRec &ch = c->chunks[c->staged++];
-      if (ch.n_rows > 0)
-        g.c[g.n++] = IngestChunk{ch.token_idx, ch.x, ch.topk_id, ch.topk_w, ch.row0, ch.n_rows,
-                                 ch.replica};
-    }
+    IngestGroup g;
+    c->staged = stage_group(c, c->staged, upto, &g);
     HIPCHK(c, launch_ingest(c->arena, g, c->cfg.top_k, c->cfg.n_local_experts,
-                            c->cfg.max_tokens_per_replica, xrb, c->d_err, s));
+                            c->cfg.max_tokens_per_replica, x_row_bytes(c->cfg), c->d_err, s));
     if (s == c->ingest) c->ingest_tail = nullptr;
   }
   return CEP_OK;
@@ -308,8 +319,15 @@ int launch_pending(cep_ctx *c) {
     HIPCHK(c, hipStreamWaitEvent(s, c->ev_ingest[slot], 0));
   }
   if (b.phases) HIPCHK(c, hipEventRecord(b.ev_start, s));
-  {
-    const int rc = stage_chunks(c, (int64_t)c->chunks.size(), s);
+  // a small batch's routing launch stages its chunks itself
+  IngestGroup grp;
+  const int64_t n_chunks = (int64_t)c->chunks.size();
+  const bool in_route = stage_group(c, c->staged, n_chunks, &grp) == n_chunks &&
+                        stage_in_route(grp, b.row0, b.n_rows, k);
+  if (in_route) {
+    c->staged = n_chunks;
+  } else {
+    const int rc = stage_chunks(c, n_chunks, s);
     if (rc != CEP_OK) return rc;
   }
   // 256-row bf16 tiles: the scan may move small remainders to 64-row tiles
@@ -318,7 +336,8 @@ int launch_pending(cep_ctx *c) {
   const int split_tiles = split ? 2 * E : 0;
   const int list2 = batch_list2(c->wk, A, P, E);
   const int grid_tiles = std::min(c->max_tiles, batch_tiles(A, list2, P, E));
-  HIPCHK(c, launch_route(c->arena, sc, b.row0, b.n_rows, k, E, A, P, c->max_mpad, c->max_tiles,
+  HIPCHK(c, launch_route(c->arena, sc, in_route ? &grp : nullptr, cfg.max_tokens_per_replica,
+                         x_row_bytes(cfg), b.row0, b.n_rows, k, E, A, P, c->max_mpad, c->max_tiles,
                          c->fetched_mask, cfg.x_dtype, c->wk, d, split ? c->n_cu : 0,
                          2 * I / kBf16TileN, list2, c->d_err, s));
   if (b.phases) HIPCHK(c, hipEventRecord(b.ev_phase[0], s));
@@ -1085,16 +1104,18 @@ CEP_API int cep_ffn_noalloc(cep_ctx *c, int replica, int n_rows, int n_pairs,
     if (pass == 0) continue;
 
     // the same kernels as a one-chunk wait-all layer, on stream s
-    IngestGroup g{};
+    IngestGroup g;
     g.c[0] = IngestChunk{token_idx, x, topk_id, topk_w, 0, n_rows, replica};
     g.n = 1;
-    const size_t xrb = (size_t)d * (cfg.x_dtype == CEP_F32 ? 4 : 2);
-    HIPCHK(c, launch_ingest(a, g, k, E, cfg.max_tokens_per_replica, xrb, c->d_err, s));
+    const size_t xrb = x_row_bytes(cfg);
+    const bool in_route = stage_in_route(g, 0, n_rows, k);
+    if (!in_route)
+      HIPCHK(c, launch_ingest(a, g, k, E, cfg.max_tokens_per_replica, xrb, c->d_err, s));
     const bool split = c->wk == kWBf16 && A == kBf16TileM;
     const int split_tiles = split ? 2 * E : 0;
     const int list2 = batch_list2(c->wk, A, P, E);
     const int tiles = std::min(tiles_cap, batch_tiles(A, list2, P, E));
-    HIPCHK(c, launch_route(a, sc, 0, n_rows, k, E, A, P, mpad, tiles_cap, 0, cfg.x_dtype, c->wk,
+    HIPCHK(c, launch_route(a, sc, in_route ? &g : nullptr, cfg.max_tokens_per_replica, xrb, 0, n_rows, k, E, A, P, mpad, tiles_cap, 0, cfg.x_dtype, c->wk,
                            d, split ? c->n_cu : 0, 2 * I / kBf16TileN, list2, c->d_err, s));
     BlobTable bt{};
     for (int e = 0; e < E; ++e) bt.blob[e] = c->w_res + (size_t)e * c->L.bytes;
