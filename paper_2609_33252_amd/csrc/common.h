@@ -80,37 +80,66 @@ struct BlobLayout {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 constexpr int kBf16SmallTileM = 64;  // bf16 tile for batches with few rows per expert
-// Such batches with at least kBf16VarMinRows pairs per local expert on
-// average run both GEMMs in 128-row tiles over the same 64-aligned layout:
-// an expert's rows in tiles of 128, the last of them a 64-row half tile when
-// at most 64 rows remain (a hot expert then reads its weights once per 128
-// rows instead of once per 64)
-constexpr int kBf16VarTileM = 128;
-constexpr int kBf16VarMinRows = 64;
-// e4m3 / MXFP4 batches of row alignment 128 with fewer pairs per local expert
-// than this run in 64-row tiles
+constexpr int kBf16VarTileM = 128;   // bf16 tile for mid-size batches
+// pairs per local expert from which e4m3 / MXFP4 batches may run in 128-row
+// instead of 64-row tiles
 constexpr int kRowsSmallTile = 64;
 
-// Per-expert row alignment A of one batch's grouped layout = M tile of the
-// GEMMs that run it.  bf16 batches with fewer than one large tile of rows
-// per local expert on average use the small tile: the GEMMs then stream the
-// weights with four times as many workgroups.  Both bf16 tiles accumulate K
-// in the same order with the same MFMA, so results do not depend on it.
-inline int batch_align(int wk, int pairs, int n_experts) {
-  if (wk != kWBf16) return pairs >= kFp8LargeTileM * n_experts ? kFp8LargeTileM : kFp8TileM;
-  return pairs >= kBf16TileM * n_experts ? kBf16TileM : kBf16SmallTileM;
-}
 // The scan's second tile list of each kind (resident / fetched experts):
-// none; kListVar 128-row tiles (64-row alignment); kListSorted the same tiles
+// none; kListVar 128-row tiles, an expert's last one a 64-row half when at
+// most 64 rows remain (64-row alignment); kListSorted the same 64-row tiles
 // ordered by rows, most first; kListHalf 64-row tiles (128-row alignment).
 enum : int { kListNone = 0, kListVar = 1, kListSorted = 2, kListHalf = 3 };
-inline int batch_list2(int wk, int align, int pairs, int n_experts) {
-  if (wk != kWBf16)
-    return align == kFp8TileM && pairs < kRowsSmallTile * n_experts ? kListHalf : kListNone;
-  if (align != kBf16SmallTileM) return kListNone;
-  // smaller bf16 batches stream the weights: both GEMMs run the 64-row tiles
-  // ordered by rows, one work item per workgroup in that order
-  return pairs >= kBf16VarMinRows * n_experts ? kListVar : kListSorted;
+
+// Tiles of one batch: the per-expert row alignment A of its grouped layout
+// (the M tile of its first list) and the second list it runs, if any.
+struct BatchPlan {
+  int align, list2;
+};
+
+// Work items of a GEMM1 launch in m-row, n-column tiles, expected for
+// `pairs` spread over the experts: an expert's last tile is half full.
+inline double expected_items(int pairs, int n_experts, int m, int n, int n_cols) {
+  const double tiles = (double)pairs / m + 0.5 * n_experts;
+  return (tiles > n_experts ? tiles : n_experts) * n_cols / n;
+}
+
+// Which tiles run a batch (n1: GEMM1's packed columns, 2 * d_ff).  Every
+// choice computes each output in the same K order with the same MFMA, so
+// results do not depend on it.
+//
+// 256-row tiles from 256 pairs per local expert on, if they occupy at least
+// 0.55 of the CUs or the batch is large anyway (512 pairs per expert with
+// bf16, whose callers see the 256-aligned layout of such batches in
+// cep_get_batch_routing, else 1024): below that half the chip idles for the
+// launch.  8 experts, GEMM1 + GEMM2: bf16 d 2048, I 1024, 377 rows per expert
+// (128 items) 102 us against 76 in 128-row tiles, 520 rows (160 items) 109
+// against 114; d 256, I 128, 388 rows 43 against 17 us; e4m3 d 1024, I 512,
+// 388 rows (32 items) 45 against 24.
+//
+// bf16 below that: 128-row tiles when there are 64 pairs per expert and they
+// give every CU an item, else the weight-streaming 64-row tiles by rows (one
+// work item per workgroup in list order), whose items are smaller: d 2048, I
+// 1024: 127 rows (192 items) 53 against 42 us, 192 rows (256 items) 54
+// against 54; d 256, I 128: 24 us at 127 rows (16 items) against 15.
+inline BatchPlan batch_plan(int wk, int pairs, int n_experts, int n1, int n_cu) {
+  const double items256 = expected_items(pairs, n_experts, 256, 256, n1);
+  const bool large = pairs >= (wk == kWBf16 ? 512 : 1024) * n_experts ||
+                     (pairs >= 256 * n_experts && items256 >= 0.55 * n_cu);
+  if (wk != kWBf16) {
+    if (large) return {kFp8LargeTileM, kListNone};
+    // 128-row tiles from kRowsSmallTile pairs per expert on, if they give
+    // every CU an item, else 64-row tiles (8 experts, d 2048, I 1024, 119 rows:
+    // MXFP4 25 against 40 us, e4m3 equal)
+    const int n = wk == kWMx ? 256 : 128;  // columns of the 128-row tiles
+    const bool mid = pairs >= kRowsSmallTile * n_experts &&
+                     expected_items(pairs, n_experts, 128, n, n1) >= n_cu;
+    return {kFp8TileM, mid ? kListNone : kListHalf};
+  }
+  if (large) return {kBf16TileM, kListNone};
+  const bool var = pairs >= 64 * n_experts &&
+                   expected_items(pairs, n_experts, kBf16VarTileM, 128, n1) >= n_cu;
+  return {kBf16SmallTileM, var ? kListVar : kListSorted};
 }
 // Upper bound of a batch's M tiles: the GEMMs' grids
 inline int batch_tiles(int align, int list2, int pairs, int n_experts) {
@@ -190,7 +219,7 @@ struct Scratch {
   int32_t *off_pad;    // [E+1]
   Tile *tiles;         // [4][max_tiles]: list 2*f + r for resident (f = 0) or
                        // fetched (f = 1) experts; r = 1: 64-row remainder tiles
-                       // (256-row batches) or batch_list2's tiles
+                       // (256-row batches) or BatchPlan::list2's tiles
   int32_t *n_tiles;    // [4]
   int32_t *pos_of;     // [max_rows * k] grouped row of each flat pair or -1
   int32_t *perm;       // [max_mpad] flat pair of each grouped row or -1
@@ -251,7 +280,7 @@ hipError_t launch_ingest(const Arena &a, const IngestGroup &grp, int k, int E, i
 // expert's last partial tile of at most 128 rows to 64-row remainder tiles
 // when its makespan estimate for split_cu compute units and GEMM1's
 // n_tiles_n 256-wide column tiles improves.  list2: the scan's second list of
-// each kind (batch_list2).
+// each kind (BatchPlan::list2).
 // stage (may be null; stage_in_route must hold): the routing launch stages
 // the batch's chunks itself, no launch_ingest before it.
 hipError_t launch_route(const Arena &a, const Scratch &sc, const IngestGroup *stage, int t_max,
@@ -275,7 +304,7 @@ hipError_t launch_combine(const Arena &a, const Scratch &sc, int row0, int n_row
 // split_tiles > 0, up to split_tiles 64-row remainder tiles
 // gather (bf16 weights and rows only): GEMM1 reads the batch's input rows
 // (arena rows from row0) in place through the permutation instead of a
-// packed copy.  list2 (batch_list2, the scan run with the same): with
+// packed copy.  list2 (BatchPlan::list2, the scan run with the same): with
 // kListVar, kListSorted and kListHalf both GEMMs run the second list's tiles.
 hipError_t launch_gemm1(const Scratch &sc, int which, int list_cap, int grid_tiles,
                         int split_tiles, int align, int list2, const BlobTable &bt, const BlobLayout &L,

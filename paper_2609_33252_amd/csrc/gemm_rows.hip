@@ -20,8 +20,7 @@
 //     (64 batches of 24 rows per expert on two streams: 6.22 against 6.40 ms),
 //     equal under skewed routing.  All M tiles of a slice in a row (column
 //     major) was slower in both (6.52 ms).
-// BM 64 serves batches below kRowsSmallTile pairs per expert (more stages or
-// workgroups fit), BM 128 the rest.  Measured against the 128 x 256 tiles of
+// BM 64 or BM 128: batch_plan.  Measured against the 128 x 256 tiles of
 // whole rows these replace (16 experts, GEMM1 + GEMM2):
 //   e4m3  d 7168, I 2048: 33 rows per expert 165 -> 148 us, 133: 259 -> 230;
 //         d 6144, I 2560: 20 rows 230 -> 157 us; d 2048, I 1024: 32 rows

@@ -121,7 +121,7 @@ struct PlanArgs {
   int E, align, expected_pairs, max_mpad, max_tiles;
   uint64_t fetched_mask;
   int split_cu, n_tiles_n;
-  int list2;  // second list of each kind (batch_list2)
+  int list2;  // second list of each kind (BatchPlan::list2)
   uint32_t *err;
 };
 

@@ -293,7 +293,8 @@ int launch_pending(cep_ctx *c) {
   if (s != c->ingest) c->used_st |= 1u << slot;
   const Scratch &sc = c->sc[slot];
   const int P = b.n_pairs;
-  const int A = batch_align(c->wk, b.n_pairs, E);
+  const BatchPlan plan = batch_plan(c->wk, P, E, 2 * I, c->n_cu);
+  const int A = plan.align, list2 = plan.list2;
   b.align = A;
   const int tiles = std::min(c->max_tiles, (P + A - 1) / A + E);
   b.mpad_bound = std::min(c->max_mpad, tiles * A);
@@ -334,7 +335,6 @@ int launch_pending(cep_ctx *c) {
   // (at most two per expert), run by a second launch of the 64-row kernel
   const bool split = c->wk == kWBf16 && A == kBf16TileM;
   const int split_tiles = split ? 2 * E : 0;
-  const int list2 = batch_list2(c->wk, A, P, E);
   const int grid_tiles = std::min(c->max_tiles, batch_tiles(A, list2, P, E));
   HIPCHK(c, launch_route(c->arena, sc, in_route ? &grp : nullptr, cfg.max_tokens_per_replica,
                          x_row_bytes(cfg), b.row0, b.n_rows, k, E, A, P, c->max_mpad, c->max_tiles,
@@ -1052,7 +1052,8 @@ CEP_API int cep_ffn_noalloc(cep_ctx *c, int replica, int n_rows, int n_pairs,
   // the grouped rows need at most P + E*(A-1) (each expert's last tile
   // padded), rounded up to whole 256-row groups of the scale layouts
   const int P = n_pairs;
-  const int A = batch_align(c->wk, P, E);
+  const BatchPlan plan = batch_plan(c->wk, P, E, 2 * I, c->n_cu);
+  const int A = plan.align, list2 = plan.list2;
   const int mpad = (int)align_up((size_t)P + (size_t)E * A, kMaxAlign);
   const int tiles_cap = (P + kMinAlign - 1) / kMinAlign + E;
   const int blocks = (int)(((long long)n_rows * k + kRoutePairs - 1) / kRoutePairs);
@@ -1113,7 +1114,6 @@ CEP_API int cep_ffn_noalloc(cep_ctx *c, int replica, int n_rows, int n_pairs,
       HIPCHK(c, launch_ingest(a, g, k, E, cfg.max_tokens_per_replica, xrb, c->d_err, s));
     const bool split = c->wk == kWBf16 && A == kBf16TileM;
     const int split_tiles = split ? 2 * E : 0;
-    const int list2 = batch_list2(c->wk, A, P, E);
     const int tiles = std::min(tiles_cap, batch_tiles(A, list2, P, E));
     HIPCHK(c, launch_route(a, sc, in_route ? &g : nullptr, cfg.max_tokens_per_replica, xrb, 0, n_rows, k, E, A, P, mpad, tiles_cap, 0, cfg.x_dtype, c->wk,
                            d, split ? c->n_cu : 0, 2 * I / kBf16TileN, list2, c->d_err, s));

@@ -56,3 +56,42 @@ def test_row_counts_at_tile_edges(name, shape, tiles):
     run.close()
     assert m["align"] == 128 and list(m["cnt"]) == cnt
     U.check(wl, got)
+
+
+# Shapes on both sides of the lines between the tile choices of a batch
+# (batch_plan): few work items and many, for the pairs per expert at which the
+# choice then differs.  (preset, overrides, tokens per replica)
+PLANS = [
+    ("sync_d4096", dict(d=256, I=128, E=8, Eg=16, k=4), 256),     # bf16, 128 rows, few items
+    ("sync_d4096", dict(d=256, I=128, E=8, Eg=16, k=4), 800),     # 400 rows: not 256-row tiles
+    ("sync_d4096", dict(d=512, I=2048, E=16, Eg=32, k=2), 1200),  # 150 rows, 128-row tiles
+    ("sync_d4096", dict(d=256, I=2560, E=8, Eg=16, k=4), 640),    # 320 rows, 256-row tiles
+    # (a last-bit difference of an h element can move its e4m3 code, by up to
+    # 1/8 of the element: 3 sigma / 8 of a row of norm sigma sqrt(I), 3.3e-2 of
+    # it at I = 128 beside the per-row bound of 4e-2, 1.7e-2 at I = 512)
+    ("fp8_fetch_d6144", dict(d=256, I=512, E=8, Eg=16, k=4), 800),
+    ("fp8_fetch_d6144", dict(d=256, I=2560, E=8, Eg=16, k=4), 640),
+    ("mxfp4_dsv4flash_d4096", dict(d=256, I=512, E=8, Eg=16, k=4), 400),
+    ("mxfp4_dsv4flash_d4096", dict(d=256, I=2560, E=12, Eg=24, k=4), 300),
+    ("mxfp4_dsv4flash_d4096", dict(d=256, I=2560, E=8, Eg=16, k=4), 640),
+]
+
+
+@pytest.mark.parametrize("i", range(len(PLANS)))
+def test_tile_choice_lines(i):
+    name, over, T = PLANS[i]
+    print(f"case {name} {over} T={T}", flush=True)
+    wl = W.generate(name, 40 + i, R=2, T=T, cpr=2, zipf=None, fetch_frac=0.0, **over)
+    run = harness.Runner(wl, n_streams=2)
+    run.run(policy=cep.CEP_WAIT_ALL)
+    torch.cuda.synchronize()
+    cep.cep_get_status(run.ctx)
+    a = run.out.cpu().numpy()
+    run.out.zero_()
+    run.run(policy=cep.CEP_PER_CHUNK, n_streams=2)  # other tiles, the same bits
+    torch.cuda.synchronize()
+    cep.cep_get_status(run.ctx)
+    b = run.out.cpu().numpy()
+    run.close()
+    U.check(wl, a)
+    assert np.array_equal(a, b)
