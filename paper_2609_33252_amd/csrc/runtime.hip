@@ -76,8 +76,10 @@ struct cep_ctx {
   hipStream_t st[8] = {};
   hipStream_t copy = nullptr;  // the fetch's copies when the caller gives no stream
   // slot streams that ran batches (or hold arrival waits) since the last
-  // layer barrier; the next layer's staging waits for exactly these
+  // layer barrier, which joins exactly these into the ingest stream
   unsigned used_st = 0;
+  // slot streams already ordered after this layer's start
+  unsigned started_st = 0;
   Scratch sc[8] = {};
   std::vector<void *> allocs;
   // policy
@@ -255,6 +257,33 @@ hipStream_t pending_stream(const cep_ctx *c) {
   return c->n_streams == 1 ? c->ingest : c->st[pending_slot(c)];
 }
 
+// Orders slot stream s after the start of the layer (ev_origin on the ingest
+// stream: after the previous layer's batches, which read the arena), once per
+// layer: a wait on an event of another stream costs the host 12 us, a record
+// 1.6, a kernel launch 4.  (With a wait before every batch and every slot
+// joined into both the caller's and the ingest stream, six batches on four
+// streams took 345 us of host time per layer; now 165.)
+int start_slot(cep_ctx *c, int slot, hipStream_t s) {
+  if (s == c->ingest || ((c->started_st >> slot) & 1)) return CEP_OK;
+  HIPCHK(c, hipStreamWaitEvent(s, c->ev_origin, 0));
+  c->started_st |= 1u << slot;
+  c->used_st |= 1u << slot;
+  return CEP_OK;
+}
+
+// Makes the ingest stream wait for every used slot stream.
+int join_slots(cep_ctx *c) {
+  for (int i = 0; i < c->cfg.n_streams; ++i) {
+    if ((c->used_st >> i) & 1) {
+      HIPCHK(c, hipEventRecord(c->ev_ingest[i], c->st[i]));
+      HIPCHK(c, hipStreamWaitEvent(c->ingest, c->ev_ingest[i], 0));
+      c->ingest_tail = nullptr;
+      c->used_st &= ~(1u << i);
+    }
+  }
+  return CEP_OK;
+}
+
 // Experts that have pairs routed to them but no weights this layer: neither
 // resident nor fetched (copied or read in place).
 uint64_t missing_experts(const cep_ctx *c) {
@@ -290,7 +319,6 @@ int launch_pending(cep_ctx *c) {
   // one stream: batches run on the ingest stream itself, in submission
   // order after their chunks' staging, without a cross-stream hop
   hipStream_t s = pending_stream(c);
-  if (s != c->ingest) c->used_st |= 1u << slot;
   const Scratch &sc = c->sc[slot];
   const int P = b.n_pairs;
   const BatchPlan plan = batch_plan(c->wk, P, E, 2 * I, c->n_cu);
@@ -311,14 +339,10 @@ int launch_pending(cep_ctx *c) {
     return fail(c, CEP_EHIP, "hipEventCreate failed");
 
   // the batch's chunks' arrival waits already sit on this stream (enqueued
-  // at submit); the ingest stream carries the layer's start (after the
-  // previous layer's batches, which read the arena), which the batch stream
-  // follows; then it stages every chunk submitted so far (the batch's, and
-  // chunks without local pairs before it) in one launch per group
-  if (s != c->ingest) {
-    HIPCHK(c, hipEventRecord(c->ev_ingest[slot], c->ingest));
-    HIPCHK(c, hipStreamWaitEvent(s, c->ev_ingest[slot], 0));
-  }
+  // at submit); the stream follows the layer's start, then stages every chunk
+  // submitted so far (the batch's, and chunks without local pairs before it)
+  // in one launch per group
+  if (const int rc = start_slot(c, slot, s); rc != CEP_OK) return rc;
   if (b.phases) HIPCHK(c, hipEventRecord(b.ev_start, s));
   // a small batch's routing launch stages its chunks itself
   IngestGroup grp;
@@ -606,13 +630,9 @@ CEP_API int cep_begin_layer(cep_ctx *c, uint32_t generation, int n_replicas,
   // the stream carries one marker fewer between layers.
   hipEvent_t prev_tail = c->used_st == 0 ? c->ingest_tail : nullptr;
   // the previous layer's batches may still read the arena: stage after them
-  for (int i = 0; i < c->cfg.n_streams; ++i) {
-    if ((c->used_st >> i) & 1) {
-      HIPCHK(c, hipEventRecord(c->ev_ingest[i], c->st[i]));
-      HIPCHK(c, hipStreamWaitEvent(c->ingest, c->ev_ingest[i], 0));
-    }
-  }
-  c->used_st = 0;
+  // (the layer barrier has joined their streams into the ingest stream)
+  if (const int rc = join_slots(c); rc != CEP_OK) return rc;
+  c->started_st = 0;
   free_batch_records(c);
   c->timing_used[0] = c->timing_used[1] = 0;
   c->gen = generation;
@@ -811,22 +831,15 @@ CEP_API int cep_combine(cep_ctx *c, hipStream_t s, hipEvent_t *done) {
   // arrival waits sit on the stream of the batch that would have held them
   if (c->staged < (int64_t)c->chunks.size()) {
     hipStream_t ps = pending_stream(c);
-    if (ps != c->ingest) {
-      HIPCHK(c, hipEventRecord(c->ev_ingest[pending_slot(c)], c->ingest));
-      HIPCHK(c, hipStreamWaitEvent(ps, c->ev_ingest[pending_slot(c)], 0));
-      c->used_st |= 1u << pending_slot(c);
-    }
+    rc = start_slot(c, pending_slot(c), ps);
+    if (rc != CEP_OK) return rc;
     rc = stage_chunks(c, (int64_t)c->chunks.size(), ps);
     if (rc != CEP_OK) return rc;
   }
   // every batch of the layer ran on a used slot stream or on the ingest
-  // stream
-  for (int i = 0; i < c->cfg.n_streams; ++i) {
-    if ((c->used_st >> i) & 1) {
-      HIPCHK(c, hipEventRecord(c->ev_ingest[i], c->st[i]));
-      HIPCHK(c, hipStreamWaitEvent(s, c->ev_ingest[i], 0));
-    }
-  }
+  // stream, which now follows them all (the next layer's start with it)
+  rc = join_slots(c);
+  if (rc != CEP_OK) return rc;
   if (s != c->ingest) {
     // a batch end event with no kernel after it already marks the end of
     // the ingest stream's work: one marker fewer between layers
