@@ -81,15 +81,17 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 constexpr int kBf16SmallTileM = 64;  // bf16 tile for batches with few rows per expert
 constexpr int kBf16VarTileM = 128;   // bf16 tile for mid-size batches
-// pairs per local expert from which e4m3 / MXFP4 batches may run in 128-row
-// instead of 64-row tiles
+constexpr int kRowsSmallM = 64, kRowsMidM = 160;  // rows of kListHalf, kListMid tiles
+// pairs per local expert from which such batches may run in the larger ones
 constexpr int kRowsSmallTile = 64;
 
 // The scan's second tile list of each kind (resident / fetched experts):
 // none; kListVar 128-row tiles, an expert's last one a 64-row half when at
 // most 64 rows remain (64-row alignment); kListSorted the same 64-row tiles
-// ordered by rows, most first; kListHalf 64-row tiles (128-row alignment).
-enum : int { kListNone = 0, kListVar = 1, kListSorted = 2, kListHalf = 3 };
+// ordered by rows, most first; kListHalf 64-row tiles of e4m3 / MXFP4 batches and
+// kListMid 160-row tiles of e4m3 batches (128-row alignment; only rows that
+// exist are loaded).
+enum : int { kListNone = 0, kListVar = 1, kListSorted = 2, kListHalf = 3, kListMid = 4 };
 
 // Tiles of one batch: the per-expert row alignment A of its grouped layout
 // (the M tile of its first list) and the second list it runs, if any.
@@ -128,13 +130,15 @@ inline BatchPlan batch_plan(int wk, int pairs, int n_experts, int n1, int n_cu) 
                      (pairs >= 256 * n_experts && items256 >= 0.55 * n_cu);
   if (wk != kWBf16) {
     if (large) return {kFp8LargeTileM, kListNone};
-    // 128-row tiles from kRowsSmallTile pairs per expert on, if they give
-    // every CU an item, else 64-row tiles (8 experts, d 2048, I 1024, 119 rows:
-    // MXFP4 25 against 40 us, e4m3 equal)
-    const int n = wk == kWMx ? 256 : 128;  // columns of the 128-row tiles
+    // the larger tiles (e4m3 160 rows x 128 columns, MXFP4 128 x 256) from
+    // kRowsSmallTile pairs per expert on, if they give every CU an item, else
+    // 64-row tiles (8 experts, d 2048, I 1024, 119 rows: MXFP4 25 against 40
+    // us, e4m3 equal)
+    const bool fp8 = wk == kWFp8;
     const bool mid = pairs >= kRowsSmallTile * n_experts &&
-                     expected_items(pairs, n_experts, 128, n, n1) >= n_cu;
-    return {kFp8TileM, mid ? kListNone : kListHalf};
+                     expected_items(pairs, n_experts, fp8 ? kRowsMidM : kFp8TileM,
+                                    fp8 ? 128 : 256, n1) >= n_cu;
+    return {kFp8TileM, !mid ? kListHalf : fp8 ? kListMid : kListNone};
   }
   if (large) return {kBf16TileM, kListNone};
   const bool var = pairs >= 64 * n_experts &&
@@ -143,7 +147,7 @@ inline BatchPlan batch_plan(int wk, int pairs, int n_experts, int n1, int n_cu) 
 }
 // Upper bound of a batch's M tiles: the GEMMs' grids
 inline int batch_tiles(int align, int list2, int pairs, int n_experts) {
-  const int m = list2 == kListHalf ? 64 : align;
+  const int m = list2 == kListHalf ? kRowsSmallM : list2 == kListMid ? kRowsMidM : align;
   return (pairs + m - 1) / m + n_experts;
 }
 constexpr int kMinAlign = 64;

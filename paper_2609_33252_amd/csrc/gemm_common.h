@@ -431,7 +431,7 @@ hipError_t launch_fp8(const GemmArgs &g, int grid_tiles, hipStream_t s);
 template <bool SWIGLU>
 hipError_t launch_mx(const GemmArgs &g, int grid_tiles, hipStream_t s);
 // e4m3 (fp8) or MXFP4 GEMM of a batch of row alignment 128: its 64-row
-// (small) or 128-row tiles
+// (small) or larger tiles (160 rows for e4m3, 128 for MXFP4)
 template <bool SWIGLU>
 hipError_t launch_rows(const GemmArgs &g, int grid_tiles, bool fp8, bool small, hipStream_t s);
 

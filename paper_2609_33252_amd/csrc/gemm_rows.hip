@@ -20,9 +20,14 @@
 //     (64 batches of 24 rows per expert on two streams: 6.22 against 6.40 ms),
 //     equal under skewed routing.  All M tiles of a slice in a row (column
 //     major) was slower in both (6.52 ms).
-// BM 64 or BM 128: batch_plan.  Measured against the 128 x 256 tiles of
-// whole rows these replace (16 experts, GEMM1 + GEMM2):
-//   e4m3  d 7168, I 2048: 33 rows per expert 165 -> 148 us, 133: 259 -> 230;
+// BM 64, or 160 (e4m3) or 128 (MXFP4) rows: batch_plan.  160 rows are the most
+// that let two workgroups share a CU; a batch of 130 rows per expert then needs
+// one tile per expert where 128 rows need two, the second of them a pass over
+// the weights for a few rows (16 experts, d 7168, I 2048, 133 rows: GEMM1 + GEMM2
+// 227 -> 189 us).  A 160 x 256 MXFP4 tile spills registers.
+// Measured against the 128 x 256 tiles of whole rows that this file replaced
+// (16 experts, GEMM1 + GEMM2):
+//   e4m3  d 7168, I 2048: 33 rows per expert 165 -> 148 us, 133: 259 -> 189;
 //         d 6144, I 2560: 20 rows 230 -> 157 us; d 2048, I 1024: 32 rows
 //         49 -> 28 us
 //   MXFP4 d 7168, I 2048: 29 rows 106 -> 93 us; d 2048, I 1024: 32 rows
@@ -70,14 +75,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_rows(GemmArgs g) {
   constexpr int CHB = BB / 16;            // 16-byte chunks of it
   constexpr int A_LD = BM / 8 / NW;       // row load segments per wave, at most
   constexpr int B_LD = BN * BB / 1024 / NW;
-  constexpr int AG = BM > 128 ? BM / 128 : 1;  // 128-row scale groups
+  constexpr int AG = BM > 128 ? 2 : 1;  // 128-row scale groups a tile touches
   constexpr int PER_MAX = A_LD + B_LD + 1;
   static_assert(B_LD * 1024 * NW == BN * BB, "weight loads split evenly over the waves");
   static_assert(STAGES == 2 || STAGES == 3, "wait counts below");
   static_assert(WN % 64 == 0, "a wave's columns hold whole gate/up groups");
-  static_assert(8 % WGM == 0, "a fragment's 128-row scale group is a constant");
+  static_assert(BM % (16 * WGM) == 0 && BM % (8 * NW) == 0 && BM <= 160, "whole fragments, two scale groups");
   int mt, nt;
-  if (!row_item<FP8 || BM == 128>(*g.n_tiles, g.N / BN, &mt, &nt)) return;
+  if (!row_item<FP8 || BM != 64>(*g.n_tiles, g.N / BN, &mt, &nt)) return;
   const Tile t = g.tiles[mt];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -213,8 +218,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_rows(GemmArgs g) {
     for (int i = 0; i < FM; ++i) {
       if ((i * WGM + wm) * 16 >= rows) break;  // uniform over the wave
       const i32x8 a = read8(sA[buf], (i * WGM + wm) * 16 + r16);
-      const int f = (f0 + i * WGM + wm) & 7;
-      const uint2 sai = sa[i * WGM / 8];
+      const int fg = f0 + i * WGM + wm, f = fg & 7;
+      const uint2 sai = sa[AG > 1 && fg >= 8 ? AG - 1 : 0];
       const int sx = (int)((f < 4 ? sai.x : sai.y) >> (8 * (f & 3)));  // byte 0: this fragment's scale
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
@@ -317,7 +322,7 @@ hipError_t launch_rows(const GemmArgs &g, int grid_tiles, bool fp8, bool small, 
   if (g.N % 256 || g.K % 128 || g.K > kMaxDim || g.s_ld % 256) return hipErrorInvalidValue;
   if (fp8) {
     if (small) return launch_as<true, 64, 128, 8, 4, 3, 2, SWIGLU>(g, grid_tiles, s);
-    return launch_as<true, 128, 128, 8, 4, 2, 2, SWIGLU>(g, grid_tiles, s);
+    return launch_as<true, 160, 128, 4, 2, 2, 2, SWIGLU>(g, grid_tiles, s);
   }
   if (small) return launch_as<false, 64, 128, 4, 4, 2, 4, SWIGLU>(g, grid_tiles, s);
   return launch_as<false, 128, 256, 4, 2, 2, 2, SWIGLU>(g, grid_tiles, s);

@@ -187,7 +187,8 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
     const int n2 = rem                       ? tiles_of(r, kBf16SmallTileM)
                    : a.list2 == kListVar     ? tiles_of(c, kBf16VarTileM)
                    : a.list2 == kListSorted  ? nall
-                   : a.list2 == kListHalf    ? tiles_of(c, 64)
+                   : a.list2 == kListHalf    ? tiles_of(c, kRowsSmallM)
+                   : a.list2 == kListMid     ? tiles_of(c, kRowsMidM)
                                              : 0;
     const int so = wave_scan(c), sp = wave_scan(nall << ash);
     int s1[2], s2[2], sf[2];
@@ -279,11 +280,12 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
         list2[ti] = Tile{x, row0, rows, 0};
       }
     }
-    if (a.list2 == kListHalf) {
-      for (int q = lane; q * 64 < c; q += 64) {
-        const int ti = rt0 + q, row0 = pad + q * 64;
-        if (ti >= a.max_tiles || row0 + 64 > a.max_mpad) break;
-        list2[ti] = Tile{x, row0, min(64, c - q * 64), 0};
+    if (a.list2 == kListHalf || a.list2 == kListMid) {
+      const int m = a.list2 == kListHalf ? kRowsSmallM : kRowsMidM;
+      for (int q = lane; q * m < c; q += 64) {
+        const int ti = rt0 + q, row0 = pad + q * m, rows = min(m, c - q * m);
+        if (ti >= a.max_tiles || row0 + rows > a.max_mpad) break;
+        list2[ti] = Tile{x, row0, rows, 0};
       }
     }
     if (rem) {

@@ -1,7 +1,7 @@
 """Few-row tiles of the e4m3 and MXFP4 GEMMs at their edges: experts whose row
 counts sit at the edges of the 8-row load segments, the 16-row fragments and
-the 64- and 128-row tiles, every row against the oracle (the bounds of
-_util.check).  The K loops have one, two, three and six steps."""
+the 64-, 128- and 160-row tiles, every row against the oracle (the bounds of
+_util.check).  The K loops have one, two, three, six and 22 steps."""
 import numpy as np
 import pytest
 import torch
@@ -13,9 +13,13 @@ from . import _util as U
 pytestmark = pytest.mark.gpu
 
 # rows per expert: the 64-row tiles (fewer than 64 pairs per expert on
-# average) and the 128-row tiles
+# average) and larger counts
 COUNTS = {"rows64": [1, 8, 9, 16, 17, 0, 64, 65, 128, 129, 63, 7],
-          "rows128": [127, 128, 129, 1, 112, 113, 0, 256, 257, 64, 15, 240]}
+          "rows128": [127, 128, 129, 1, 112, 113, 0, 256, 257, 64, 15, 240],
+          # with I 2816 the batch has enough work items for the larger tiles
+          # (160 rows for e4m3: tiles that start at row 32, 64 and 96 of a
+          # 128-row scale group)
+          "rows160": [159, 160, 161, 1, 320, 321, 0, 480, 15, 240, 176, 145]}
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -31,11 +35,14 @@ def _gpu():
 def test_row_counts_at_tile_edges(name, shape, tiles):
     cnt = COUNTS[tiles]
     E, (d, I) = len(cnt), shape
+    if tiles == "rows160":
+        I = 2816
     print(f"case {name} d={d} I={I} {tiles}", flush=True)
     # every expert local, so every token is delivered; then one local slot per
     # token up to the counts, and a second one (of the next expert) for some
-    wl = W.generate(name, 31, d=d, I=I, E=E, Eg=E, k=2, R=1, T=2048, cpr=1, fetch_frac=0.0)
-    ids = np.full((2048, 2), -1, np.int32)
+    T = 4096
+    wl = W.generate(name, 31, d=d, I=I, E=E, Eg=E, k=2, R=1, T=T, cpr=1, fetch_frac=0.0)
+    ids = np.full((T, 2), -1, np.int32)
     own = np.repeat(np.arange(E, dtype=np.int32), cnt)
     order = np.random.default_rng(5).permutation(len(own))
     half = len(own) // 2
@@ -43,8 +50,8 @@ def test_row_counts_at_tile_edges(name, shape, tiles):
     rest = own[order[len(own) - half:]]
     both = rest != ids[:half, 0]  # a token's slots name distinct experts
     ids[:half, 1][both] = rest[both]
-    ids[1024:1024 + int((~both).sum()), 0] = rest[~both]
-    wl.topk_local = ids.reshape(1, 2048, 2)
+    ids[T // 2:T // 2 + int((~both).sum()), 0] = rest[~both]
+    wl.topk_local = ids.reshape(1, T, 2)
     assert wl.n_pairs == sum(cnt)
     assert (wl.n_pairs < 64 * E) == (tiles == "rows64")
     run = harness.Runner(wl, n_streams=1, record_routing=True, use_fetch=False)
