@@ -19,7 +19,7 @@ OBJ = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
 SOURCES = ["route.hip", "gemm.hip", "gemm_bf16.hip", "gemm_fp8.hip", "gemm_mx.hip",
-           "gemm_rows.hip", "runtime.hip", "profile.cpp", "oewf.cpp"]
+           "gemm_rows.hip", "gemm_rows_bf16.hip", "runtime.hip", "profile.cpp", "oewf.cpp"]
 # Per-source extra flags.  The e4m3 GEMMs promote every MFMA result with
 # VALU arithmetic; taking MFMA results in VGPRs saves one accvgpr read per
 # promoted element.

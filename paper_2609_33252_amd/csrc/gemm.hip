@@ -67,7 +67,7 @@ hipError_t launch_gemm1(const Scratch &sc, int which, int list_cap, int grid_til
   g.out = sc.h;
   g.out_s = sc.hs;
   if (list2 != kListNone) g = second_list(g, sc, which, list_cap);
-  if (list2 == kListVar) return launch_bf16_var<true>(g, grid_tiles, s);
+  if (list2 == kListVar) return launch_bf16_mid<true>(g, grid_tiles, s);
   if (list2 == kListSorted) return launch_bf16_stream(g, grid_tiles, s);
   return launch_any<true>(g, grid_tiles, split_tiles, align, wk, list2 == kListHalf, sc, which,
                           list_cap, s);
@@ -91,7 +91,7 @@ hipError_t launch_gemm2(const Scratch &sc, int which, int list_cap, int grid_til
   g.out = sc.y;
   g.wrow = sc.wrow;
   if (list2 != kListNone) g = second_list(g, sc, which, list_cap);
-  if (list2 == kListVar) return launch_bf16_var<false>(g, grid_tiles, s);
+  if (list2 == kListVar) return launch_bf16_mid<false>(g, grid_tiles, s);
   if (list2 == kListSorted) return launch_bf16_stream2(g, grid_tiles, s);
   return launch_any<false>(g, grid_tiles, split_tiles, align, wk, list2 == kListHalf, sc, which,
                           list_cap, s);

@@ -7,19 +7,14 @@
 // projection and scales each row by its routing coefficient (the one place
 // the coefficient is applied).
 //
-// One kernel template, three uses:
-//   large batches: 256 x 256 tile, K steps of 32 through 4 LDS stages, one
-//     workgroup per CU -- MFMA-bound, each 16-byte LDS read feeds 4 MFMAs;
-//   small batches (few rows per expert): 64 x 128 tile, K steps of 64 through
-//     3 stages, two workgroups per CU -- weight-streaming (HBM) bound, sized
-//     for many weight bytes in flight per CU;
-//   mid-size batches (VAR): 128 x 128 tiles whose last tile per expert may be
-//     a 64-row half (it loads and multiplies its first 64 rows only), the
-//     weights three stages deep and the rows two, so that two workgroups
-//     still fit a CU: a hot expert streams its weights once per 128 rows;
-//   weight-streaming batches (LIN): the small tile's schedule over 64-row
-//     tiles listed by rows, one work item per workgroup in list order, each
-//     wave loading only its 8-row segments that hold rows.
+// One kernel template, two uses:
+//   large batches (PIPE): 256 x 256 tile, K steps of 32 through 4 LDS stages,
+//     one workgroup per CU -- MFMA-bound, each 16-byte LDS read feeds 4 MFMAs;
+//   weight-streaming batches (few rows per expert) and remainder tiles: 64-row
+//     tiles in list order, K steps of 64 through 3 stages, two workgroups per
+//     CU -- HBM bound, sized for many weight bytes in flight per CU, each wave
+//     loading only its 8-row segments that hold rows.
+// Mid-size batches: gemm_rows_bf16.hip.
 // All accumulate each output over K in the same order (ascending 16-wide
 // steps of v_mfma_f32_32x32x16_bf16), so a row's result does not depend on
 // which tile its batch used.  With bf16 token rows GEMM1 runs as GATHER: its
@@ -64,13 +59,9 @@ __device__ inline void static_for(F &&f) {
 // tile): fragments are read right before their MFMAs and loads run STAGES-1
 // steps ahead, which keeps more weight bytes in flight per LDS byte.
 template <int BM, int BN, int BK, int STAGES, int OCC, bool PIPE, bool SWIGLU, int WGM = 2,
-          int NW = 4, int GM = kGroupM, bool GATHER = false, bool VAR = false, int ASTG = 0,
-          bool LIN = false>
+          int NW = 4, int GM = kGroupM, bool GATHER = false>
 __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
   static_assert(BK == 32 || BK == 64, "LDS swizzle covers 4 or 8 chunks per row");
-  static_assert(!VAR || (!PIPE && WGM == 2 && BM == 128), "VAR: 128-row tile, two wave rows");
-  static_assert(ASTG == 0 || (ASTG == 2 && !PIPE && STAGES >= 3), "A ring: all stages or two");
-  constexpr int AS = ASTG ? ASTG : STAGES;  // depth of the A ring (B: STAGES)
   static_assert(STAGES >= 3 && STAGES <= 8, "wait counts below");
   constexpr int CH = BK / 8;                  // 16-byte chunks per LDS row
   constexpr int RPS = 1024 / (BK * 2);        // rows per 1 KB load segment
@@ -94,7 +85,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
   const int n_live = *g.n_tiles;
   for (int it = 0;; ++it) {
   int mt, nt;
-  if constexpr (LIN) {
+  if constexpr (!PIPE) {
     // work item = workgroup id, tile-major (every column slice of tile 0
     // first): the hardware starts the items in list order
     if (it > 0) return;
@@ -113,7 +104,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
   const char *Ag = GATHER ? nullptr : (const char *)(g.A + (size_t)t.row0 * K * 2);
   const char *Bg = (const char *)(blob_of(g.bt, t.expert) + g.b_off);
 
-  __shared__ u32x4 sA[AS][BM * CH];
+  __shared__ u32x4 sA[STAGES][BM * CH];
   __shared__ u32x4 sB[STAGES][BN * CH];
   // GEMM2 of the non-PIPE tiles: direct output rows (GemmArgs::ydst; the
   // 256-row tile's epilogue has no registers to spare and gets none)
@@ -150,7 +141,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
   }
 #define CEP_DMA_A(kt)                                                               \
   {                                                                                 \
-    const int buf_ = (kt) % AS;                                                     \
+    const int buf_ = (kt) % STAGES;                                                 \
     _Pragma("unroll") for (int i = 0; i < NAL_; ++i) {                              \
       const int seg = wid * SEGW_ + i;                                              \
       dma16(GATHER ? arow[i] + (size_t)(kt) * BK * 2                                \
@@ -175,11 +166,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
 
-  // First row of A fragment i of this wave.  VAR interleaves the waves'
-  // fragments (i*64 + wm*32) so that a half tile's 64 rows are fragment 0
-  // of every wave.  Every fragment row r = base + lane%32 has
-  // swz(r) == swz(lane % 32) because the bases are multiples of 32.
-  auto frow = [&](int i) { return VAR ? i * (BM / FM) + wm * 32 : wm * WM + i * 32; };
+  // First row of A fragment i of this wave.  Every fragment row r = base +
+  // lane%32 has swz(r) == swz(lane % 32) because the bases are multiples of 32.
+  auto frow = [&](int i) { return wm * WM + i * 32; };
   const int rsw = ((lane & 31) >> SH) & (CH - 1);
 #define CEP_LOAD_FRAG(fa_, fb_, abuf_, bbuf_, kk_, nfa_)                            \
   {                                                                                 \
@@ -192,8 +181,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
 
   constexpr int KK = BK / 16;
   static_assert(!PIPE || KK % 2 == 0, "fragment double buffer alternates per sub-step");
-  // a VAR tile of at most BM/2 rows loads and multiplies its first half only
-  const bool half = VAR && t.rows <= BM / 2;
   if constexpr (PIPE) {
     constexpr int NAL_ = A_LD, SEGW_ = A_LD;
     const char *arow[NAL_];
@@ -318,27 +305,15 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
     // the tail's reloads must land before the workgroup's LDS is released
     wait_vmcnt<0>();
   } else {
-    // NFA A fragments per wave and NAL_ A loads per wave and step, the
-    // first NAL_ of the wave's SEGW_ load segments (wave w loads segments
-    // w*SEGW_ ..: all of them, or for a VAR half tile those of its first
-    // BM/2 rows); the wave's vmcnt waits count its own loads per step.
-    auto run = [&](auto nfa_c, auto nal_c, auto segw_c) {
-      constexpr int NFA = decltype(nfa_c)::value, NAL_ = decltype(nal_c)::value;
-      constexpr int SEGW_ = decltype(segw_c)::value;
+    // NAL_ A loads per wave and step, the first NAL_ of the wave's A_LD load
+    // segments (wave w loads segments w*A_LD ..); the wave's vmcnt waits
+    // count its own loads per step.
+    auto run = [&](auto nal_c) {
+      constexpr int NAL_ = decltype(nal_c)::value, SEGW_ = A_LD;
       constexpr int PERX = NAL_ + B_LD;
       const char *arow[NAL_ > 0 ? NAL_ : 1];
       CEP_AROWS(arow)
-      if constexpr (ASTG == 2) {
-        // B (weights, from HBM) runs STAGES-1 steps ahead, A (rows, mostly
-        // L2 hits) one step ahead in a ring of two: the top of step j issues
-        // A(j+1), then B(j+STAGES-1), into buffers last read in step j-1.
-        // The prologue is "step -1" after B(0 .. STAGES-3).
-#pragma unroll
-        for (int s = 0; s < STAGES - 2; ++s)
-          if (s < nk) CEP_DMA_B(s);
-        CEP_DMA_A(0);
-        if (STAGES - 2 < nk) CEP_DMA_B(STAGES - 2);
-      } else {
+      {
         // Stage s is issued at the top of step s - STAGES + 1, into the
         // buffer of stage s - STAGES, which every wave finished reading in
         // step s - STAGES (before this step's barrier).
@@ -347,14 +322,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
           if (s < nk) CEP_DMA_STAGE(s);
       }
       for (int kt = 0; kt < nk; ++kt) {
-        if constexpr (ASTG == 2) {
-          // A(kt) and B(kt) are done when only B(kt+STAGES-2), issued after
-          // A(kt) at the top of step kt-1, may be outstanding
-          if (kt + STAGES - 2 < nk)
-            wait_vmcnt<B_LD>();
-          else
-            wait_vmcnt<0>();
-        } else {
+        {
           // this thread's loads of step kt are done when at most the loads
           // of the steps issued after it are outstanding
           wait_stages<PERX, STAGES - 2>(min(nk - 1, kt + STAGES - 2) - kt);
@@ -362,19 +330,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
         // every wave's loads of step kt landed; step kt-1 fully consumed.  A
         // bare barrier: __syncthreads() would also drain the later loads.
         __builtin_amdgcn_s_barrier();
-        if constexpr (ASTG == 2) {
-          if (kt + 1 < nk) CEP_DMA_A(kt + 1);
-          if (kt + STAGES - 1 < nk) CEP_DMA_B(kt + STAGES - 1);
-        } else {
-          if (kt + STAGES - 1 < nk) CEP_DMA_STAGE(kt + STAGES - 1);
-        }
-        const int acur = kt % AS, cur = kt % STAGES;
+        if (kt + STAGES - 1 < nk) CEP_DMA_STAGE(kt + STAGES - 1);
+        const int cur = kt % STAGES;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
           bf16x8 fa[FM], fb[FN];
-          CEP_LOAD_FRAG(fa, fb, acur, cur, kk, NFA);
+          CEP_LOAD_FRAG(fa, fb, cur, cur, kk, FM);
 #pragma unroll
-          for (int i = 0; i < NFA; ++i)
+          for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
               acc[i][j] =
@@ -382,29 +345,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
         }
       }
     };
-    // LIN: a wave loads only those of its load segments (RPS rows each)
-    // that hold rows of the tile (its MFMAs then read stale LDS rows for the
-    // rest, whose outputs are never stored): a tile of a few rows requests
-    // little more than its weights
-    auto run_rows = [&](auto nfa_c, auto segw_c) {
-      constexpr int SEGW = decltype(segw_c)::value;
-      if constexpr (LIN) {
-        const int n = min(SEGW, max(0, (t.rows - wid * SEGW * RPS + RPS - 1) / RPS));
-        static_for<SEGW + 1>([&](auto k) {
-          if (n == decltype(k)::value) run(nfa_c, k, segw_c);
-        });
-      } else {
-        run(nfa_c, segw_c, segw_c);
-      }
-    };
-    if constexpr (VAR) {
-      if (half)
-        run_rows(ic<1>{}, ic<A_LD / 2>{});
-      else
-        run_rows(ic<FM>{}, ic<A_LD>{});
-    } else {
-      run_rows(ic<FM>{}, ic<A_LD>{});
-    }
+    // a wave loads only those of its load segments (RPS rows each) that hold
+    // rows of the tile (its MFMAs then read stale LDS rows for the rest, whose
+    // outputs are never stored): a tile of a few rows requests little more
+    // than its weights
+    const int n = min(A_LD, max(0, (t.rows - wid * A_LD * RPS + RPS - 1) / RPS));
+    static_for<A_LD + 1>([&](auto k) {
+      if (n == decltype(k)::value) run(k);
+    });
   }
 #undef CEP_LOAD_FRAG
 #undef CEP_DMA_STAGE
@@ -428,7 +376,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
   if constexpr (PIPE && !SWIGLU) {
     // float32 outputs straight from the accumulators: one store instruction
     // writes 32 consecutive columns (128 bytes) of two rows
-    static_assert(WGM == 2 && !VAR, "two wave rows");
+    static_assert(WGM == 2, "two wave rows");
     float *Y = (float *)g.out;
     float wc[16], wx[16];
     coef16(0, wc);
@@ -461,7 +409,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
     // two-byte pieces).  Chunk c of a staged row r sits at c ^ (4 * ((r/4) % 4)),
     // so the two half-waves of one element write (rows r and r+4) use
     // different banks.
-    static_assert(WGM == 2 && !VAR, "staged epilogue: two wave rows");
+    static_assert(WGM == 2, "staged epilogue: two wave rows");
     constexpr int CB = BN / 2;   // h columns of the tile
     constexpr int CPR = CB / 8;  // 16-byte chunks per output row
     constexpr int WCB = WN / 2;  // h columns of one wave
@@ -523,7 +471,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
     __bf16 *H = (__bf16 *)g.out;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      if (half && i > 0) break;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int rt = frow(i) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
@@ -554,8 +501,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
   }
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
-    if (half && i > 0) break;
-    if (!SWIGLU && i + 1 < FM && !half) {
+    if (!SWIGLU && i + 1 < FM) {
       coef16(i + 1, wx);
       dst16(i + 1, dx);
     }
@@ -604,13 +550,6 @@ hipError_t launch_bf16_as(const GemmArgs &g, int grid_tiles, int align, hipStrea
     const int grid = std::min(balanced_grid(grid_tiles, kGroupM, g.N / BN), persistent_grid());
     hipLaunchKernelGGL((k_gemm_bf16<kBf16TileM, BN, 32, 4, 1, true, SWIGLU, 2, 4, kGroupM, GATHER>),
                        dim3(grid), dim3(256), 0, s, g);
-  } else if (align == kBf16SmallTileM) {
-    constexpr int BN = 128;
-    if (g.N % BN || g.K % 64) return hipErrorInvalidValue;
-    const int grid = balanced_grid(grid_tiles, kGroupM, g.N / BN);
-    hipLaunchKernelGGL(
-        (k_gemm_bf16<kBf16SmallTileM, BN, 64, 3, 2, false, SWIGLU, 2, 4, kGroupM, GATHER>),
-        dim3(grid), dim3(256), 0, s, g);
   } else {
     return hipErrorInvalidValue;
   }
@@ -620,9 +559,9 @@ hipError_t launch_bf16_as(const GemmArgs &g, int grid_tiles, int align, hipStrea
 // Remainder tiles run alone after the 256-row launch and touch a few experts,
 // so few workgroups stream their weights; each CU's streaming rate is bounded,
 // so they use 64-column tiles: twice the workgroups of the streaming tile, half
-// the weight bytes each (GEMM1's gate and up halves meet in LDS).  LIN: only
-// the 8-row segments that hold rows are loaded (a remainder averages half a
-// tile or less): 44 -> 40 and 27 -> 24.5 us on the 4096-wide layer, 112 -> 102
+// the weight bytes each (GEMM1's gate and up halves meet in LDS).  Loading
+// only the 8-row segments that hold rows (a remainder averages half a tile or
+// less) took 44 -> 40 and 27 -> 24.5 us on the 4096-wide layer, 112 -> 102
 // and 60 -> 57 us on the 7168-wide threshold batches.  (Four and six stages: no
 // change, +30 %.)
 template <bool SWIGLU, bool GATHER>
@@ -631,7 +570,7 @@ hipError_t launch_bf16_rem_as(const GemmArgs &g, int grid_tiles, hipStream_t s) 
   if (g.N % BN || g.K % 64) return hipErrorInvalidValue;
   const int grid = grid_tiles * (g.N / BN);
   hipLaunchKernelGGL((k_gemm_bf16<kBf16SmallTileM, BN, 64, 3, 2, false, SWIGLU, 2, 4, kGroupM,
-                                  GATHER, false, 0, true>),
+                                  GATHER>),
                      dim3(grid), dim3(256), 0, s, g);
   return hipGetLastError();
 }
@@ -660,28 +599,6 @@ hipError_t launch_bf16(const GemmArgs &g, int grid_tiles, int align, hipStream_t
   return launch_bf16_as<SWIGLU, false>(g, grid_tiles, align, s);
 }
 
-template <bool SWIGLU, bool GATHER>
-hipError_t launch_bf16_var_as(const GemmArgs &g, int grid_tiles, hipStream_t s) {
-  constexpr int BN = 128;
-  if (g.N % BN || g.K % 64) return hipErrorInvalidValue;
-  const int grid = balanced_grid(grid_tiles, kGroupM, g.N / BN);
-  hipLaunchKernelGGL(
-      (k_gemm_bf16<kBf16VarTileM, BN, 64, 3, 2, false, SWIGLU, 2, 4, kGroupM, GATHER, true, 2>),
-      dim3(grid), dim3(256), 0, s, g);
-  return hipGetLastError();
-}
-
-template <bool SWIGLU>
-hipError_t launch_bf16_var(const GemmArgs &g, int grid_tiles, hipStream_t s) {
-  if constexpr (SWIGLU) {
-    if (g.A == nullptr) {
-      if (!g.xrow || !g.perm || g.k < 1) return hipErrorInvalidValue;
-      return launch_bf16_var_as<true, true>(g, grid_tiles, s);
-    }
-  }
-  return launch_bf16_var_as<SWIGLU, false>(g, grid_tiles, s);
-}
-
 // Weight-streaming batches (a few hundred pairs over all local experts, one
 // of them hot).  A CU's load rate bounds these launches, and it counts every
 // byte requested, rows from L2 as much as weights from HBM, so a launch lasts
@@ -699,7 +616,7 @@ hipError_t launch_bf16_stream_as(const GemmArgs &g, int grid_tiles, hipStream_t 
   if (g.N % BN || g.K % 64) return hipErrorInvalidValue;
   const int grid = grid_tiles * (g.N / BN);
   hipLaunchKernelGGL((k_gemm_bf16<kBf16SmallTileM, BN, 64, 3, 2, false, true, 2, 4, kGroupM,
-                                  GATHER, false, 0, true>),
+                                  GATHER>),
                      dim3(grid), dim3(256), 0, s, g);
   return hipGetLastError();
 }
@@ -707,8 +624,7 @@ hipError_t launch_bf16_stream_as(const GemmArgs &g, int grid_tiles, hipStream_t 
 template <int BN>
 hipError_t launch_bf16_stream2_as(const GemmArgs &g, int grid_tiles, hipStream_t s) {
   if (g.N % BN || g.K % 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_gemm_bf16<kBf16SmallTileM, BN, 64, 3, 2, false, false, 2, 4, kGroupM,
-                                  false, false, 0, true>),
+  hipLaunchKernelGGL((k_gemm_bf16<kBf16SmallTileM, BN, 64, 3, 2, false, false, 2, 4, kGroupM>),
                      dim3(grid_tiles * (g.N / BN)), dim3(256), 0, s, g);
   return hipGetLastError();
 }
@@ -730,8 +646,6 @@ hipError_t launch_bf16_stream(const GemmArgs &g, int grid_tiles, hipStream_t s) 
   return launch_bf16_stream_as<false>(g, grid_tiles, s);
 }
 
-template hipError_t launch_bf16_var<true>(const GemmArgs &, int, hipStream_t);
-template hipError_t launch_bf16_var<false>(const GemmArgs &, int, hipStream_t);
 template hipError_t launch_bf16<true>(const GemmArgs &, int, int, hipStream_t);
 template hipError_t launch_bf16<false>(const GemmArgs &, int, int, hipStream_t);
 

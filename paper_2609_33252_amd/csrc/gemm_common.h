@@ -109,6 +109,24 @@ inline int balanced_grid(int grid_tiles, int gm, int n_tiles_n) {
 // eight, at equal or better speed (measured on the bf16 and MXFP4 GEMM1 of
 // the DeepSeek-V4-Flash-shaped and 4096-wide workloads).
 constexpr int kGroupM = 4;
+// Work item of this workgroup, dealt to the XCDs: groups of kGroupM M tiles x
+// all column tiles, M fastest (tile_of); the order's pieces of kGroupM items
+// (one column slice of a group) go round the XCDs, so that a group's tiles, a
+// hot expert's among them, load every XCD alike and share each weight slice in
+// one XCD's L2.  Returns false for a surplus workgroup of deal_grid.
+__device__ inline bool deal_item(int n_live, int n_tiles_n, int *mt, int *nt) {
+  const int j = blockIdx.x >> 3;
+  const int L = ((j / kGroupM) * 8 + (blockIdx.x & 7)) * kGroupM + j % kGroupM;
+  if (L >= n_live * n_tiles_n) return false;
+  tile_of<kGroupM>(L, n_live, n_tiles_n, mt, nt);
+  return true;
+}
+// Grid for deal_item: whole pieces of kGroupM items for every XCD
+inline int deal_grid(int grid_tiles, int n_tiles_n) {
+  const int per = 8 * kGroupM;
+  return (grid_tiles * n_tiles_n + per - 1) / per * per;
+}
+
 // M tiles per group when whole groups go to one XCD (work_item_xg): eight,
 // so that 32 workgroups run an 8 x 4 block (as few distinct panels as 4 x 8)
 // and groups of 20 or 24 column tiles are a whole number of rounds.
@@ -418,9 +436,9 @@ hipError_t launch_bf16(const GemmArgs &g, int grid_tiles, int align, hipStream_t
 // bf16 GEMM over the scan's 64-row remainder tiles
 template <bool SWIGLU>
 hipError_t launch_bf16_rem(const GemmArgs &g, int grid_tiles, hipStream_t s);
-// bf16 GEMM over a list of 128-row and 64-row (half) tiles
+// bf16 GEMM of a mid-size batch over its kListVar tiles (gemm_rows_bf16.hip)
 template <bool SWIGLU>
-hipError_t launch_bf16_var(const GemmArgs &g, int grid_tiles, hipStream_t s);
+hipError_t launch_bf16_mid(const GemmArgs &g, int grid_tiles, hipStream_t s);
 // bf16 GEMM1 (SwiGLU) of a weight-streaming batch over its 64-row tiles
 // ordered by rows, one 64-column work item per workgroup in list order
 hipError_t launch_bf16_stream(const GemmArgs &g, int grid_tiles, hipStream_t s);

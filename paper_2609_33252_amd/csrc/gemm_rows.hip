@@ -11,7 +11,7 @@
 //     from 64 pairs per expert on), so that a batch of a few experts has
 //     several work items per CU, and two to four workgroups share a CU: the
 //     loads of one proceed while another waits at its step's barrier;
-//   * the work order (row_item) keeps an expert's tiles of one column slice on
+//   * the work order (deal_item) keeps an expert's tiles of one column slice on
 //     one XCD at one time, which then reads that weight slice once, and deals
 //     the slices round to the XCDs: with contiguous shares a hot expert's
 //     tiles fell to one XCD (e4m3, Zipf(1.2) routing, 130 rows per expert:
@@ -48,21 +48,6 @@ namespace {
 
 __device__ inline int b_swz_mx(int r) { return (r & 1) | ((r >> 1) & 2); }
 
-// Work item of this workgroup: groups of kGroupM M tiles x all column tiles,
-// M fastest (tile_of).  SPREAD deals the order's pieces of kGroupM items (one
-// column slice of a group) round to the XCDs, so that a group's tiles, a hot
-// expert's among them, load every XCD alike; otherwise each XCD takes one
-// contiguous share (work_item).
-template <bool SPREAD>
-__device__ inline bool row_item(int n_live, int n_tiles_n, int *mt, int *nt) {
-  if constexpr (!SPREAD) return work_item<kGroupM, false>(0, n_live, n_tiles_n, mt, nt);
-  const int j = blockIdx.x >> 3;
-  const int L = ((j / kGroupM) * 8 + (blockIdx.x & 7)) * kGroupM + j % kGroupM;
-  if (L >= n_live * n_tiles_n) return false;
-  tile_of<kGroupM>(L, n_live, n_tiles_n, mt, nt);
-  return true;
-}
-
 // FP8: e4m3 weights (float32 block scales, promoted per K block), else MXFP4
 // (E8M0 scales applied by the MFMA).  WGM x WGN waves; wave row wm owns the
 // 16-row fragments wm, wm + WGM, ...; wave column wn the columns
@@ -82,7 +67,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_rows(GemmArgs g) {
   static_assert(WN % 64 == 0, "a wave's columns hold whole gate/up groups");
   static_assert(BM % (16 * WGM) == 0 && BM % (8 * NW) == 0 && BM <= 160, "whole fragments, two scale groups");
   int mt, nt;
-  if (!row_item<FP8 || BM != 64>(*g.n_tiles, g.N / BN, &mt, &nt)) return;
+  constexpr bool SPREAD = FP8 || BM != 64;
+  if (!(SPREAD ? deal_item(*g.n_tiles, g.N / BN, &mt, &nt)
+               : work_item<kGroupM, false>(0, *g.n_tiles, g.N / BN, &mt, &nt)))
+    return;
   const Tile t = g.tiles[mt];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -307,9 +295,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_rows(GemmArgs g) {
 
 template <bool FP8, int BM, int BN, int NW, int WGM, int STAGES, int OCC, bool SWIGLU>
 hipError_t launch_as(const GemmArgs &g, int grid_tiles, hipStream_t s) {
-  // whole pieces of kGroupM items for every XCD
-  const int per = 8 * kGroupM;
-  const int grid = (grid_tiles * (g.N / BN) + per - 1) / per * per;
+  const int grid = deal_grid(grid_tiles, g.N / BN);
   hipLaunchKernelGGL((k_gemm_rows<FP8, BM, BN, NW, WGM, STAGES, OCC, SWIGLU>), dim3(grid),
                      dim3(64 * NW), 0, s, g);
   return hipGetLastError();

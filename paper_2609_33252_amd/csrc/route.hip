@@ -269,14 +269,11 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
       }
     }
     if (a.list2 == kListVar) {
-      // the second list holds the 128-row tiles; a tile of more than 64
-      // rows spans 128 rows of the expert's 64-aligned region
       for (int q = lane; q * kBf16VarTileM < c; q += 64) {
         const int ti = rt0 + q;
         const int rows = min(kBf16VarTileM, c - q * kBf16VarTileM);
         const int row0 = pad + q * kBf16VarTileM;
-        const int span = rows > kBf16VarTileM / 2 ? kBf16VarTileM : kBf16VarTileM / 2;
-        if (ti >= a.max_tiles || row0 + span > a.max_mpad) break;
+        if (ti >= a.max_tiles || row0 + rows > a.max_mpad) break;
         list2[ti] = Tile{x, row0, rows, 0};
       }
     }
