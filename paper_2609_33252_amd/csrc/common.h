@@ -86,10 +86,10 @@ constexpr int kRowsSmallM = 64, kRowsMidM = 160;  // rows of kListHalf, kListMid
 constexpr int kRowsSmallTile = 64;
 
 // The scan's second tile list of each kind (resident / fetched experts):
-// none; kListVar 128-row tiles (64-row alignment); kListSorted the
-// 64-row tiles ordered by rows, most first; kListHalf 64-row tiles of e4m3 / MXFP4 batches and
-// kListMid 160-row tiles of e4m3 batches (128-row alignment; only rows that
-// exist are loaded).
+// none; kListVar 128-row tiles (64-row alignment); kListSorted the 64-row tiles
+// ordered by rows, most first; kListHalf 64-row tiles of e4m3 / MXFP4 batches
+// and kListMid 160-row tiles of e4m3 batches (128-row alignment; only rows
+// that exist are loaded).
 enum : int { kListNone = 0, kListVar = 1, kListSorted = 2, kListHalf = 3, kListMid = 4 };
 
 // Tiles of one batch: the per-expert row alignment A of its grouped layout

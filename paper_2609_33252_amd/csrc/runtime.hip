@@ -112,7 +112,7 @@ struct cep_ctx {
   // where each expert's weights are read from in this layer (null: none)
   const uint8_t *blob_ptr[kMaxExperts] = {};
   hipEvent_t ev_fetch_start = nullptr, ev_fetch_ready = nullptr;
-  // sync-only events, one set per slot (re-recorded per batch)
+  // sync-only events, one per slot (re-recorded at each layer barrier)
   hipEvent_t ev_ingest[8] = {};
   hipEvent_t ev_layer_done = nullptr, ev_layer_ingest = nullptr;
   // the last event recorded on the ingest stream with no kernel after it
