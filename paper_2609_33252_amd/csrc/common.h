@@ -187,6 +187,14 @@ __host__ __device__ inline size_t mx_row_scale_offset(int R, int b, int s_ld) {
          ((R & 127) >> 4);
 }
 
+// 128-row groups of that layout which the rows [row0, row0 + rows) of a tile
+// touch.  A tile loads the scales of these groups only: the buffer ends with
+// the last group of the grouped rows, so a load of "this group and the next"
+// would pass its end in the last K step of a tile in the last group.
+__host__ __device__ inline int mx_row_groups(int row0, int rows) {
+  return ((row0 & 127) + rows + 127) >> 7;
+}
+
 // E8M0 weight scales in a blob (B = [N][K] packed weights, N a multiple of
 // 256): for each 256-column tile and K step of 128 one 1 KB record holding,
 // for the wave of column group wn (64 columns), the lane of K block g and

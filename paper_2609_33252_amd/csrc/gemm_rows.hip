@@ -85,6 +85,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_rows(GemmArgs g) {
   // row scales of K step kb: 512 bytes per 128-row group
   const char *Asg = (const char *)g.As + (size_t)(row0 >> 7) * 512;
   const size_t as_step = (size_t)(g.s_ld >> 7) * 512;
+  const int n_as = 32 * (AG > 1 ? mx_row_groups(row0, rows) : 1);  // lanes that load them
   // MXFP4 weight scales: per K step the tile's 4 * BN bytes of the 1 KB record
   const char *Bsg = (const char *)(blob + g.bs_off) + (size_t)(nt * BN / 256) * nkb * 1024 +
                     (nt * BN % 256) * 4;
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_rows(GemmArgs g) {
       dma16_s(Bg + (size_t)kb * (FP8 ? 128 : 1024), off,
               __builtin_amdgcn_readfirstlane(lds_offset(&sB[buf][seg * 64])));
     }
-    if (wid == 0 && lane < AG * 32)
+    if (wid == 0 && lane < n_as)
       dma16_s(Asg + (size_t)kb * as_step, lane * 16,
               __builtin_amdgcn_readfirstlane(lds_offset(&sAs[buf][0])));
     if (!FP8 && wid == 1 && lane < BN / 4)
