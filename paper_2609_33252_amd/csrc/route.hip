@@ -213,13 +213,14 @@ __device__ void plan_batch(const Scratch &sc, PlanLds &L, const PlanArgs &a, int
       L.nfull[0] = sf[0];
       L.nfull[1] = sf[1];
       if (so != a.expected_pairs) atomicOr(a.err, kErrPairCount);
+      // a batch with more pairs than its buffers hold (n_pairs too low) runs no
+      // tile: its lists would have entries that nothing below writes
       const int t0[4] = {s1[0], s2[0], s1[1], s2[1]};
       bool over = sp > a.max_mpad;
 #pragma unroll
-      for (int l = 0; l < 4; ++l) {
-        over = over || t0[l] > a.max_tiles;
-        sc.n_tiles[l] = min(t0[l], a.max_tiles);
-      }
+      for (int l = 0; l < 4; ++l) over = over || t0[l] > a.max_tiles;
+#pragma unroll
+      for (int l = 0; l < 4; ++l) sc.n_tiles[l] = over ? 0 : t0[l];
       if (over) atomicOr(a.err, kErrOverflow);
     }
   }

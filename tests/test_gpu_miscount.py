@@ -60,3 +60,42 @@ def test_tile_in_the_last_scale_group():
     run.close()
     tok = np.stack([np.zeros(1200, np.int64), np.arange(1200)], axis=1)
     U.check(wl, got[0, :1200], tokens=tok)
+
+
+@pytest.mark.parametrize("T", [1024, 4096], ids=["one-block routing", "two-kernel routing"])
+@pytest.mark.parametrize("call", ["layer", "noalloc"])
+@pytest.mark.parametrize("name", ["sync_d4096", "tiny", "fp8_fetch_d6144",
+                                  "mxfp4_dsv4flash_d4096"])
+def test_batch_beyond_its_buffers_runs_no_tile(name, call, T):
+    # 1007 pairs declared as 100: more tiles, and without a context's slack more
+    # grouped rows, than the buffers hold.  Every token has one local pair, whose
+    # output row GEMM2 itself would write: rows stay as they were, or are zero
+    # where the pair has no grouped row
+    wl = _workload(name, 256, 128, [1] * 7 + [1000], T)
+    run = harness.Runner(wl, n_streams=1, use_fetch=False, max_pairs=100)
+    ch = run.chunks[0]
+
+    def go(c):
+        run.out.fill_(5.0)
+        if call == "noalloc":
+            cep.cep_ffn_noalloc(run.ctx, c.replica, c.n_rows, c.n_pairs, c.token_idx, c.x, c.ids,
+                                c.w, run.out, torch.cuda.current_stream())
+        else:
+            run.run_subset([run.chunks.index(c)])
+        torch.cuda.synchronize()
+
+    ch.n_pairs = 100
+    go(ch)
+    with pytest.raises(cep.CepError) as e:
+        cep.cep_get_status(run.ctx)
+    assert "n_pairs mismatch" in str(e.value) and "capacity" in str(e.value)
+    out = run.out[0, :1007].cpu().numpy()
+    assert np.all((out == 5.0).all(axis=1) | (out == 0.0).all(axis=1))
+    run.chunks.append(_part(ch, 90))
+    go(run.chunks[1])
+    cep.cep_get_status(run.ctx)
+    got = run.out.cpu().numpy()
+    run.close()
+    tok = np.stack([np.zeros(90, np.int64), np.arange(90)], axis=1)
+    U.check(wl, got[0, :90], tokens=tok)
+    assert np.all(got[0, 90:] == 5.0)
