@@ -241,9 +241,10 @@ size_t x_row_bytes(const cep_config &cfg) {
 int stage_chunks(cep_ctx *c, int64_t upto, hipStream_t s) {
   while (c->staged < upto) {
     IngestGroup g;
-    c->staged = stage_group(c, c->staged, upto, &g);
+    const int64_t next = stage_group(c, c->staged, upto, &g);
     HIPCHK(c, launch_ingest(c->arena, g, c->cfg.top_k, c->cfg.n_local_experts,
                             c->cfg.max_tokens_per_replica, x_row_bytes(c->cfg), c->d_err, s));
+    c->staged = next;  // a launch that failed leaves its chunks to a retry
     if (s == c->ingest) c->ingest_tail = nullptr;
   }
   return CEP_OK;
@@ -349,9 +350,7 @@ int launch_pending(cep_ctx *c) {
   const int64_t n_chunks = (int64_t)c->chunks.size();
   const bool in_route = stage_group(c, c->staged, n_chunks, &grp) == n_chunks &&
                         stage_in_route(grp, b.row0, b.n_rows, k);
-  if (in_route) {
-    c->staged = n_chunks;
-  } else {
+  if (!in_route) {
     const int rc = stage_chunks(c, n_chunks, s);
     if (rc != CEP_OK) return rc;
   }
@@ -413,6 +412,9 @@ int launch_pending(cep_ctx *c) {
   HIPCHK(c, hipEventRecord(b.ev_end, s));
   if (s == c->ingest) c->ingest_tail = b.ev_end;
   c->batches.push_back(b);
+  // staged by the routing launch: only now, so that a batch that failed on the
+  // way here is staged again (that launch leaves no ids in the arena)
+  c->staged = n_chunks;
   c->pending_first = c->chunks.size();
   c->pending_pairs = c->pending_rows = 0;
   return CEP_OK;

@@ -29,3 +29,9 @@ def _run(tmp_path, name, *args):
 
 def test_row_scale_loads_stay_in_their_buffer(tmp_path):
     _run(tmp_path, "row_scales")
+
+
+def test_layer_order_and_retry(tmp_path):
+    # the runtime over a model of HIP's streams: layers back to back under random
+    # policies and stream counts, and launches that fail at each of their steps
+    _run(tmp_path, "layer_order", "-w", "-x", "c++")
