@@ -218,8 +218,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
       }
     };
     // GEMM1: a wave whose row fragments are not all in use runs a K loop of
-    // its own that skips them (16 experts of 316 to 516 rows, d 7168: 172 ->
-    // 164 and 252 -> 237 us; GEMM2 did not gain)
+    // its own that skips them.  Its workgroup then runs ahead of those that
+    // share its panels, which are read again.  16 experts, d 7168, I 2048, GEMM1
+    // without and with, and its HBM reads: 325 rows per expert 182 -> 173 us,
+    // 371 -> 530 MB; 520 rows 266 -> 257 us; 900 rows 378 -> 367 us, 735 -> 860
+    // MB; 1670 rows 657 -> 657 us, 1048 -> 1370 MB; 2200 rows 891 -> 869 us, 1580
+    // -> 1960 MB: the launch is not bound by those reads.  GEMM2 did not gain.
     if (!SWIGLU || nfr >= 8) {
       for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::false_type{});
     } else {

@@ -78,6 +78,10 @@ PLANS = [
     # it at I = 128 beside the per-row bound of 4e-2, 1.7e-2 at I = 512)
     ("fp8_fetch_d6144", dict(d=256, I=512, E=8, Eg=16, k=4), 800),
     ("fp8_fetch_d6144", dict(d=256, I=2560, E=8, Eg=16, k=4), 640),
+    # 256-row tiles either side of the four rounds of work items up to which GEMM1
+    # skips empty row fragments (500 and 600 rows per expert, 20 column tiles)
+    ("fp8_fetch_d6144", dict(d=256, I=2560, E=16, Eg=32, k=4), 2000),
+    ("fp8_fetch_d6144", dict(d=256, I=2560, E=16, Eg=32, k=4), 2400),
     ("mxfp4_dsv4flash_d4096", dict(d=256, I=512, E=8, Eg=16, k=4), 400),
     ("mxfp4_dsv4flash_d4096", dict(d=256, I=2560, E=12, Eg=24, k=4), 300),
     ("mxfp4_dsv4flash_d4096", dict(d=256, I=2560, E=8, Eg=16, k=4), 640),
