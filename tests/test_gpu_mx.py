@@ -56,7 +56,7 @@ def test_mxfp4_reduced_all_rows():
 
 
 def test_mxfp4_large_and_small_m_tiles_agree_bitwise():
-    # wait-all: >= 256 rows per expert (256-row tile); per chunk: 128-row tile
+    # wait-all: >= 256 rows per expert (256-row tile); per chunk: 64-row tiles
     wl = W.generate(NAME, 1, d=1024, I=512, E=4, Eg=32, R=4, T=2048, cpr=8)
     assert wl.n_pairs >= 256 * wl.cfg["E"]
     run = harness.Runner(wl, n_streams=2, record_routing=True)
@@ -128,7 +128,7 @@ def test_mxfp4_persistent_tiles_odd_k_steps_all_rows():
     # coefficients during the epilogue) with an odd number of GEMM2 K steps
     # (I = 640: five), so that a tile's last step uses ring buffer 0, the
     # buffer the next tile's first stage fills: every row against the oracle,
-    # and bitwise equal to per-chunk batches on the 4-wave 128-row tile.
+    # and bitwise equal to per-chunk batches on the 64-row tiles.
     wl = W.generate(NAME, 12, d=1024, I=640, E=4, Eg=16, R=4, T=4096, cpr=64)
     E, k = wl.cfg["E"], wl.cfg["k"]
     run = harness.Runner(wl, n_streams=1, record_routing=True, use_fetch=False)

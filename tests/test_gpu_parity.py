@@ -19,6 +19,7 @@ from oracle import policy as opol
 from oracle import routing as orout
 from paper_2609_33252_amd import cep, harness, workload as W
 
+from . import _native as N
 from . import _util as U
 
 pytestmark = pytest.mark.gpu
@@ -252,19 +253,23 @@ def test_large_and_small_m_tiles_agree_bitwise():
     U.check(wl, a)
 
 
-def test_var_tiles_agree_bitwise():
-    # 64-row bf16 batches with at least 64 pairs per local expert run both
-    # GEMMs in 128-row tiles, an expert's last tile a 64-row half when at
-    # most 64 rows remain: a hot expert spans several tiles and ends in a
-    # half tile.  Same K order as the wait-all batch's 256-row tiles and the
-    # per-chunk batches' 64-row tiles, so the same bits.
-    wl = W.generate("zipf_imbalanced_d7168", 6, d=1024, I=512, R=8, T=4096, cpr=4)
+@pytest.mark.parametrize("d,I,fetch", [(1024, 512, 0.0), (512, 2048, 0.0), (512, 2048, 0.25)])
+def test_var_tiles_agree_bitwise(d, I, fetch):
+    # bf16 batches with at least 64 pairs per local expert and a work item for
+    # every CU (d_ff 2048, not 512) run both GEMMs in 128-row tiles, loaded only
+    # as far as they hold rows: a hot expert spans several tiles and ends in one
+    # of at most 64 rows; resident and fetched experts have lists of their own.
+    # Same K order as the wait-all batch's 256-row tiles and the smaller batches'
+    # 64-row tiles, so the same bits.
+    wl = W.generate("zipf_imbalanced_d7168", 6, d=d, I=I, R=8, T=4096, cpr=4, fetch_frac=fetch)
     E, k = wl.cfg["E"], wl.cfg["k"]
     run = harness.Runner(wl, n_streams=2, record_routing=True)
     run.run(policy=cep.CEP_WAIT_ALL)
     a = _out(run)
     assert cep.cep_get_batch_routing(run.ctx, 0, E, k)["align"] == 256
-    small = var_multi_half = 0
+    fetched = np.zeros(E, bool)
+    fetched[list(wl.fetched)] = True
+    small = var = part = both = 0
     for pol, theta in ((cep.CEP_PER_CHUNK, 1), (cep.CEP_THRESHOLD, 300),
                        (cep.CEP_THRESHOLD, 600), (cep.CEP_THRESHOLD, 1200)):
         run.out.zero_()
@@ -276,21 +281,30 @@ def test_var_tiles_agree_bitwise():
             if m["align"] != 64:
                 continue
             c = m["cnt"]
-            if c.sum() < 64 * E:
+            tiles = N.tiles(wl, c.sum())
+            assert tiles in ("128", "64 by rows")
+            if tiles == "64 by rows":
                 small += 1
-            else:
-                var_multi_half += int(((c > 128) & (c % 128 > 0) & (c % 128 <= 64)).any())
+                continue
+            var += 1
+            part += int(((c > 128) & (c % 128 > 0) & (c % 128 <= 64)).any())
+            both += int((c[fetched] > 0).any() and (c[~fetched] > 0).any())
     run.close()
-    assert small > 0 and var_multi_half > 0, (small, var_multi_half)
+    assert small > 0 and (var > 0) == (I == 2048) and (part > 0) == (I == 2048), (small, var, part)
+    assert both == (var if fetch else 0)
     U.check(wl, a)
 
 
-def test_var_tiles_packed_rows_agree_bitwise():
+@pytest.mark.parametrize("I", [128, 2048])
+def test_var_tiles_packed_rows_agree_bitwise(I):
     # f32 rows are packed to bf16, so GEMM1 reads the packed copy: the
-    # wait-all batch (1536 pairs, 180-212 rows per expert: a 128-row tile,
-    # then a half or a second full tile) runs the 128-row tiles, single
-    # chunks (384 pairs) the 64-row tiles
-    wl = W.generate("tiny", 1, R=2, T=384)
+    # wait-all batch (1536 pairs, 180-212 rows per expert: a full 128-row tile
+    # and one of more or less than 64 rows) runs the 128-row tiles where they
+    # have an item for every CU (d_ff 2048), single chunks (384 pairs) the 64-row
+    # tiles
+    wl = W.generate("tiny", 1, R=2, T=384, I=I)
+    assert N.tiles(wl, wl.n_pairs) == ("128" if I == 2048 else "64 by rows")
+    assert {N.tiles(wl, wl.chunk_pairs(c)) for c in wl.chunks} == {"64 by rows"}
     E, k = wl.cfg["E"], wl.cfg["k"]
     assert 64 * E <= wl.n_pairs < 256 * E
     assert max(wl.chunk_pairs(c) for c in wl.chunks) < 64 * E
@@ -491,7 +505,7 @@ def test_fp8_persistent_tiles_odd_k_steps_all_rows():
     # the epilogue) with an odd number of K steps in GEMM2 (I = 640: five),
     # so that a tile's last step uses ring buffer 0, the buffer the next
     # tile's first stage fills: every row against the oracle, and bitwise
-    # equal to per-chunk batches on the 4-wave 128-row tile.
+    # equal to per-chunk batches on the 64-row tiles.
     wl = W.generate("fp8_fetch_d6144", 11, d=1024, I=640, E=4, Eg=16, R=4, T=4096, cpr=64)
     E, k = wl.cfg["E"], wl.cfg["k"]
     run = harness.Runner(wl, n_streams=1, record_routing=True, use_fetch=False)
@@ -541,9 +555,8 @@ def test_fp8_large_tile_all_rows_and_small_tile_bitwise():
     # The e4m3 8-wave 256-row tile (the large-batch tile of the e4m3
     # workload) over every row against the oracle: four experts of 1757 to
     # 4229 rows, each over several 256-row tiles ending in a partial one, one
-    # of them fetched.  Per-chunk batches (at most 370 pairs) run the 4-wave
-    # 128-row tile: each wave computes the same 128 x 64 block with the same
-    # K order and promotion, so the same bits.
+    # of them fetched.  Per-chunk batches (at most 370 pairs) run the 64-row
+    # tiles with the same K order and promotion, so the same bits.
     wl = W.generate("fp8_fetch_d6144", 7, d=1024, I=512, E=4, Eg=16, R=4, T=2048, cpr=8)
     E, k = wl.cfg["E"], wl.cfg["k"]
     run = harness.Runner(wl, n_streams=2, record_routing=True, use_fetch=True)

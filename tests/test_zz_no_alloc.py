@@ -10,6 +10,7 @@ import torch
 
 from paper_2609_33252_amd import cep, harness, workload as W
 
+from . import _native as N
 from . import _util as U
 
 pytestmark = pytest.mark.gpu
@@ -41,20 +42,28 @@ def _noalloc(run, i):
     return out.cpu().numpy()
 
 
+# preset, overrides, the tiles of the first and of the second, smaller call
 CASES = {
-    # bf16 weights and rows (rows read in place), 64-row and 256-row tiles
-    "bf16": ("zipf_stream_d7168", dict(d=1024, I=512, Eg=16, R=2, T=2048, cpr=2, zipf=None)),
-    # e4m3 weights (rows quantised into the scratch), 256-row then 128-row tiles
+    # bf16 weights and rows (rows read in place)
+    "bf16": ("zipf_stream_d7168", dict(d=1024, I=512, Eg=16, R=2, T=2048, cpr=2, zipf=None),
+             "256", "64 by rows"),
+    "bf16_mid": ("zipf_stream_d7168", dict(d=256, I=1920, Eg=64, R=2, T=2048, cpr=2, zipf=None),
+                 "128", "64 by rows"),
+    # e4m3 weights (rows quantised into the scratch)
     "fp8": ("fp8_fetch_d6144", dict(d=1024, I=512, E=4, Eg=16, R=2, T=2048, cpr=2,
-                                    fetch_frac=0.0)),
+                                    fetch_frac=0.0), "64", "64"),
+    "fp8_large": ("fp8_fetch_d6144", dict(d=256, I=2560, E=4, Eg=16, R=2, T=2048, cpr=2,
+                                          fetch_frac=0.0), "256", "160"),
+    "mxfp4": ("mxfp4_dsv4flash_d4096", dict(d=256, I=2560, E=8, Eg=32, R=2, T=2048, cpr=2),
+              "128", "64"),
     # float32 rows packed to bf16
-    "f32": ("tiny", dict(R=2, T=512, cpr=2)),
+    "f32": ("tiny", dict(R=2, T=512, cpr=2), "64 by rows", "64 by rows"),
 }
 
 
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_noalloc_equals_existing_entry_point(case):
-    name, kw = CASES[case]
+    name, kw, *tiles = CASES[case]
     wl = W.generate(name, 0, **kw)
     run = harness.Runner(wl, n_streams=1)
     pairs = [ch.n_pairs for ch in run.chunks]
@@ -73,6 +82,7 @@ def test_noalloc_equals_existing_entry_point(case):
     run.chunks_per_replica[small.replica] += 1
     s_idx = len(run.chunks) - 1
     assert 0 < small.n_pairs < pairs[big]
+    assert [N.tiles(wl, p) for p in (pairs[big], small.n_pairs)] == tiles
     for i in (big, s_idx):
         got = _noalloc(run, i)
         want = _existing(run, i)
