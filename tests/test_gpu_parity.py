@@ -232,6 +232,33 @@ def test_chunking_order_policy_streams_invariance_bitwise():
         assert np.array_equal(o, outs[0])
 
 
+def test_layers_back_to_back_without_synchronisation():
+    # Layers enqueued on one context with nothing waited for in between, each in
+    # its own submission order and into its own output: a slot stream must follow
+    # the previous layer, whose last batch may have run on the ingest stream (its
+    # end event then stands for this layer's start), before it writes the arena
+    # and the slot's scratch.
+    wl = W.generate("zipf_imbalanced_d7168", 3, d=2048, I=1024, T=2048, cpr=4)
+    run = harness.Runner(wl, n_streams=4)
+    cep.cep_set_phase_timing(run.ctx, False)
+    run.run(policy=cep.CEP_WAIT_ALL)
+    ref = _out(run)
+    rng = np.random.default_rng(0)
+    plan = [(cep.CEP_WAIT_ALL, 1, 1), (cep.CEP_PER_CHUNK, 1, 4), (cep.CEP_WAIT_ALL, 1, 1),
+            (cep.CEP_THRESHOLD, 700, 2), (cep.CEP_THRESHOLD, 300, 1), (cep.CEP_PER_CHUNK, 1, 3),
+            (cep.CEP_PER_CHUNK, 1, 1), (cep.CEP_THRESHOLD, 1500, 4)]
+    outs = [torch.zeros_like(run.out) for _ in plan]
+    torch.cuda.synchronize()
+    for (pol, theta, ns), o in zip(plan, outs):
+        run.run(policy=pol, theta=theta, n_streams=ns, order=list(rng.permutation(len(run.chunks))),
+                out=o, inputs_ready=True)
+    torch.cuda.synchronize()
+    cep.cep_get_status(run.ctx)
+    run.close()
+    for i, o in enumerate(outs):
+        assert np.array_equal(o.cpu().numpy(), ref), plan[i]
+
+
 def test_large_and_small_m_tiles_agree_bitwise():
     # one wait-all batch has >= 256 rows per expert (256-row M tile); single
     # chunks have ~125 (64-row M tile): same K order, same bits
