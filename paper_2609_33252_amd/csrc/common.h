@@ -15,7 +15,7 @@ constexpr int kMaxTopK = 16;
 constexpr int kMaxDim = 32768;  // largest d_model and d_ff (fp8 GEMM keeps K/128 weight scales per row in LDS)
 constexpr int kBf16TileM = 256;      // bf16 grouped GEMM tile
 constexpr int kBf16TileN = 256;
-constexpr int kFp8TileM = 128;       // e4m3 / MXFP4 grouped GEMM tile (4 waves)
+constexpr int kFp8TileM = 128;       // e4m3 / MXFP4 row alignment of few-row tiles
 constexpr int kFp8LargeTileM = 256;  // e4m3 / MXFP4 tile for large batches (8 waves)
 constexpr int kRouteThreads = 256;   // threads per routing block
 constexpr int kRoutePairs = 1024;    // flat pairs per routing block (4 rounds of 256)
@@ -110,13 +110,18 @@ inline double expected_items(int pairs, int n_experts, int m, int n, int n_cols)
 // results do not depend on it.
 //
 // 256-row tiles from 256 pairs per local expert on, if they occupy at least
-// 0.55 of the CUs or the batch is large anyway (512 pairs per expert with
-// bf16, whose callers see the 256-aligned layout of such batches in
-// cep_get_batch_routing, else 1024): below that half the chip idles for the
-// launch.  8 experts, GEMM1 + GEMM2: bf16 d 2048, I 1024, 377 rows per expert
-// (128 items) 102 us against 76 in 128-row tiles, 520 rows (160 items) 109
-// against 114; d 256, I 128, 388 rows 43 against 17 us; e4m3 d 1024, I 512,
-// 388 rows (32 items) 45 against 24.
+// 0.55 of the CUs or the batch is large anyway (1024 pairs per expert, 512
+// with bf16): below that half the chip idles for the launch.  8 experts, GEMM1
+// + GEMM2: bf16 d 2048, I 1024, 377 rows per expert (128 items) 102 us against
+// 76 in 128-row tiles, 520 rows (160 items) 109 against 114; d 256, I 128, 388
+// rows 43 against 17 us; e4m3 d 1024, I 512, 388 rows (32 items) 45 against 24.
+//
+// The bf16 line at 512 lies too low for narrow shapes.  Whole layers of 520 and
+// 900 rows per expert in 256-row tiles, and in the tiles chosen below: 8 experts
+// of d 256, I 128 92 and 95 us against 65 and 67; d 4096, I 512 217 and 251
+// against 160 and 207; 16 experts of d 4096, I 384 281 and 350 against 223 and
+// 356; 8 experts of d 4096, I 768, 900 rows 270 against 276.  A line near 1024
+// rows would serve them; it has not been moved yet.
 //
 // bf16 below that: 128-row tiles when there are 64 pairs per expert and they
 // give every CU an item, else the weight-streaming 64-row tiles by rows (one
@@ -315,8 +320,8 @@ hipError_t launch_combine(const Arena &a, const Scratch &sc, int row0, int n_row
 // split_tiles > 0, up to split_tiles 64-row remainder tiles
 // gather (bf16 weights and rows only): GEMM1 reads the batch's input rows
 // (arena rows from row0) in place through the permutation instead of a
-// packed copy.  list2 (BatchPlan::list2, the scan run with the same): with
-// kListVar, kListSorted and kListHalf both GEMMs run the second list's tiles.
+// packed copy.  list2 (BatchPlan::list2, the scan run with the same): unless
+// kListNone, both GEMMs run the second list's tiles.
 hipError_t launch_gemm1(const Scratch &sc, int which, int list_cap, int grid_tiles,
                         int split_tiles, int align, int list2, const BlobTable &bt, const BlobLayout &L,
                         int wk, int d, int I, const Arena *gather, int row0,

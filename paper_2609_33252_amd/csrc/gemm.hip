@@ -2,7 +2,7 @@
 // invocations"): GEMM1 = gate/up projection with SwiGLU (and, for e4m3
 // and MXFP4 weights, the h re-quantisation) in the epilogue; GEMM2 = down
 // projection scaled by each row's routing coefficient.  Kernels:
-// gemm_bf16.hip, gemm_fp8.hip, gemm_mx.hip, gemm_rows.hip.
+// gemm_bf16.hip, gemm_rows_bf16.hip, gemm_fp8.hip, gemm_mx.hip, gemm_rows.hip.
 #include "gemm_common.h"
 
 namespace cep {

@@ -236,7 +236,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
               __builtin_amdgcn_readfirstlane(lds_offset(&sB[buf][seg * 64])));
       }
     };
-    // sub-steps 0 .. KK-2 of the step in buffer cur
     // sub-steps 0 .. KK-2 of the step in buffer cur; with DMA, sub-step 0
     // also issues the loads of K step ks into buffer kbuf between its MFMAs
     auto early_subs = [&](int cur, auto dma_c, int ks, int kbuf) {
@@ -313,20 +312,16 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(GemmArgs g) {
       constexpr int PERX = NAL_ + B_LD;
       const char *arow[NAL_ > 0 ? NAL_ : 1];
       CEP_AROWS(arow)
-      {
-        // Stage s is issued at the top of step s - STAGES + 1, into the
-        // buffer of stage s - STAGES, which every wave finished reading in
-        // step s - STAGES (before this step's barrier).
+      // Stage s is issued at the top of step s - STAGES + 1, into the buffer
+      // of stage s - STAGES, which every wave finished reading in step
+      // s - STAGES (before this step's barrier).
 #pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s)
-          if (s < nk) CEP_DMA_STAGE(s);
-      }
+      for (int s = 0; s < STAGES - 1; ++s)
+        if (s < nk) CEP_DMA_STAGE(s);
       for (int kt = 0; kt < nk; ++kt) {
-        {
-          // this thread's loads of step kt are done when at most the loads
-          // of the steps issued after it are outstanding
-          wait_stages<PERX, STAGES - 2>(min(nk - 1, kt + STAGES - 2) - kt);
-        }
+        // this thread's loads of step kt are done when at most the loads of
+        // the steps issued after it are outstanding
+        wait_stages<PERX, STAGES - 2>(min(nk - 1, kt + STAGES - 2) - kt);
         // every wave's loads of step kt landed; step kt-1 fully consumed.  A
         // bare barrier: __syncthreads() would also drain the later loads.
         __builtin_amdgcn_s_barrier();

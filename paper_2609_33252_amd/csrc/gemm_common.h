@@ -20,8 +20,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // list (expert, first row, valid rows) built by the routing scan.
 struct GemmArgs {
   const uint8_t *A;       // grouped rows [mpad][K] (bf16 or e4m3)
-  const float *As;        // e4m3: [K/128][s_ld] row scales, k-block major;
-                          // mx: E8M0 bytes at mx_row_scale_offset
+  const float *As;        // quantised A: E8M0 bytes at mx_row_scale_offset
   int s_ld;               // quantised A: row stride of the scale matrices
   const Tile *tiles;      // tile list
   const int32_t *n_tiles; // live tiles in the list
@@ -323,7 +322,7 @@ __device__ inline int store_y_bf16_staged(const uint32_t (&yb)[8][4][2], const G
         const int r = (i & 3) * 16 + r16;  // row within the 64-row piece
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-      const int c = wn * 8 + j * 2 + (grp >> 1);  // 16-byte chunk of the row
+          const int c = wn * 8 + j * 2 + (grp >> 1);  // 16-byte chunk of the row
           uint2 *dst = (uint2 *)&st[r * 32 + (c ^ r16)] + (grp & 1);
           *dst = make_uint2(yb[i][j][0], yb[i][j][1]);
         }
@@ -434,7 +433,7 @@ __device__ inline void store_h_mx_staged(const f32x4 (&acc)[8][4], const GemmArg
   }
 }
 
-// Launchers of the two kernel families (grid from the tile bound).
+// Launchers of the kernels (grid from the tile bound).
 template <bool SWIGLU>
 hipError_t launch_bf16(const GemmArgs &g, int grid_tiles, int align, hipStream_t s);
 // bf16 GEMM over the scan's 64-row remainder tiles

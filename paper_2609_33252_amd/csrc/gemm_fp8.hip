@@ -61,9 +61,9 @@ __device__ inline f32x4 f8_mfma(const i32x8 &w, const i32x8 &x, int ox, int sx) 
 // 2-4) has one parity, and those lanes then touch sixteen distinct slots of
 // 256 bytes.
 //
-// Persistent: one workgroup per CU takes work items j,
-// j + grid/8, ... of its XCD's share.  After a tile's K loop it issues the
-// next tile's first stage into buffer 0 and loads the next tile's block
+// Persistent: one workgroup per CU takes work items j, j + grid/8, ... of its
+// XCD's share.  After a tile's K loop it issues the next tile's first stage
+// into buffer 0 and loads the next tile's block
 // scales into registers, then runs the epilogue through buffer 1 (staged
 // stores of every row, so each wave issues a fixed number S of stores), so
 // that the next tile's first loads and its memory latency overlap the
@@ -192,10 +192,10 @@ __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
     const u32x4 hi = s[row * 8 + ((grp + 4) ^ rsw)];
     return __builtin_bit_cast(i32x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  // stores each wave issues at least in an epilogue (512
-  // threads): GEMM1 256 x 128 code bytes in 16-byte pieces (4) and one
-  // scale word; GEMM2 two passes of 128 x 512 bytes (8 each; the staging
-  // counts its direct float32 rows' extra stores)
+  // stores each wave issues at least in an epilogue (512 threads): GEMM1 256 x
+  // 128 code bytes in 16-byte pieces (4) and one scale word; GEMM2 two passes
+  // of 128 x 512 bytes (8 each; the staging counts its direct float32 rows'
+  // extra stores)
   constexpr int S_EPI = SWIGLU ? 4 : 16;
   // block scales per thread (at most 8 or 2 rows of kMaxDim/BK per tile)
   constexpr int NBSV = (SWIGLU ? 8 : 2) * (kMaxDim / BK) / (64 * NW);
@@ -258,59 +258,57 @@ __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
       for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::true_type{});
     }
 
-    {
-      // GEMM2: the outputs are scaled by the coefficients (in LDS since the
-      // tile's first step) and packed to bf16 before the next tile's
-      // coefficients overwrite them
-      uint32_t yb[SWIGLU ? 1 : 8][4][2];
-      if constexpr (!SWIGLU) {
+    // GEMM2: the outputs are scaled by the coefficients (in LDS since the
+    // tile's first step) and packed to bf16 before the next tile's
+    // coefficients overwrite them
+    uint32_t yb[SWIGLU ? 1 : 8][4][2];
+    if constexpr (!SWIGLU) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) wr[i] = sW[wm * 128 + i * 16 + r16];
-        pack_y_bf16(acc, wr, yb);
-      }
-      int mt2, nt2;
-      const bool more = work_item_xg<kGroupXcd>(it + 1, n_live, ntn, &mt2, &nt2);
-      F8Tile nxt;
-      float sbv[NBSV];
-      if (more) {
-        // every wave's operand reads of the last step completed (it may
-        // have used buffer 0): the next tile's first stage may fill it
-        wait_lgkm0();
-        __builtin_amdgcn_s_barrier();
-        nxt = tile_at(mt2, nt2);
-        stage(nxt, 0, 0);
-        stage_coef(nxt, db ^ 1);
-#pragma unroll
-        for (int v = 0; v < NBSV; ++v) {
-          const int i = tid + v * 64 * NW;
-          sbv[v] = i < nbs ? nxt.bs[i] : 0.0f;
-        }
-      }
-      // epilogue through buffer 1 (sA[1], sB[1]: 32 KB each)
-      static_assert(sizeof(sA[1]) >= BM * 128 && sizeof(sA[1]) >= 64 * 512 &&
-                        sizeof(sB[1]) >= 64 * 512, "staging fits buffer 1");
-      int n_st = S_EPI;
-      if constexpr (SWIGLU)
-        store_h_mx_staged<NW, SKIP>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
-      else
-        n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0],
-                                             &sB[1][0], &sD[db][0]);
-      if (!more) return;
-      // the next tile's first stage and block scales landed once at most the
-      // epilogue's stores are outstanding
-      if constexpr (SWIGLU)
-        wait_vmcnt<S_EPI>();
-      else
-        wait_vmcnt_upto<0, 63>(n_st);
+      for (int i = 0; i < 8; ++i) wr[i] = sW[wm * 128 + i * 16 + r16];
+      pack_y_bf16(acc, wr, yb);
+    }
+    int mt2, nt2;
+    const bool more = work_item_xg<kGroupXcd>(it + 1, n_live, ntn, &mt2, &nt2);
+    F8Tile nxt;
+    float sbv[NBSV];
+    if (more) {
+      // every wave's operand reads of the last step completed (it may
+      // have used buffer 0): the next tile's first stage may fill it
+      wait_lgkm0();
+      __builtin_amdgcn_s_barrier();
+      nxt = tile_at(mt2, nt2);
+      stage(nxt, 0, 0);
+      stage_coef(nxt, db ^ 1);
 #pragma unroll
       for (int v = 0; v < NBSV; ++v) {
         const int i = tid + v * 64 * NW;
-        if (i < nbs) sBs[i] = sbv[v];
+        sbv[v] = i < nbs ? nxt.bs[i] : 0.0f;
       }
-      wait_lgkm0();  // the block scales are in LDS before the K loop's barrier
-      cur = nxt;
-      db ^= 1;
     }
+    // epilogue through buffer 1 (sA[1], sB[1]: 32 KB each)
+    static_assert(sizeof(sA[1]) >= BM * 128 && sizeof(sA[1]) >= 64 * 512 &&
+                      sizeof(sB[1]) >= 64 * 512, "staging fits buffer 1");
+    int n_st = S_EPI;
+    if constexpr (SWIGLU)
+      store_h_mx_staged<NW, SKIP>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
+    else
+      n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0], &sB[1][0],
+                                     &sD[db][0]);
+    if (!more) return;
+    // the next tile's first stage and block scales landed once at most the
+    // epilogue's stores are outstanding
+    if constexpr (SWIGLU)
+      wait_vmcnt<S_EPI>();
+    else
+      wait_vmcnt_upto<0, 63>(n_st);
+#pragma unroll
+    for (int v = 0; v < NBSV; ++v) {
+      const int i = tid + v * 64 * NW;
+      if (i < nbs) sBs[i] = sbv[v];
+    }
+    wait_lgkm0();  // the block scales are in LDS before the K loop's barrier
+    cur = nxt;
+    db ^= 1;
   }
 }
 

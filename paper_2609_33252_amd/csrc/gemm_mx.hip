@@ -257,8 +257,8 @@ __global__ __launch_bounds__(512, 1) void k_gemm_mx_persist(GemmArgs g) {
     if constexpr (SWIGLU)
       store_h_mx_staged<NW>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
     else
-      n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0],
-                                           &sY[0], &sD[db][0]);
+      n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0], &sY[0],
+                                     &sD[db][0]);
     if (!more) return;
     // the next tile's first stage (and coefficients) landed once at most the
     // epilogue's stores are outstanding; this wave's staging reads are done

@@ -1,9 +1,11 @@
 // e4m3 and MXFP4 grouped expert GEMMs of batches with few rows per expert
-// (row alignment 128: fewer than 256 pairs per local expert on average).
+// (row alignment 128: fewer than 256 pairs per local expert on average, up to
+// 1024 where 256-row tiles would leave half the CUs idle).
 //
 // Such a batch reads every touched expert's weights once for a few rows.  A CU
-// requests at most some 27 GB/s here, rows (from L2) and weights (from HBM)
-// alike, so a launch lasts as long as the bytes its busiest CU requests:
+// requests some 25 to 31 GB/s here, rows (from L2) and weights (from HBM) alike
+// (24 GB/s when everything streams from HBM), so a launch lasts as long as the
+// bytes its busiest CU requests:
 //   * rows are loaded and multiplied in the pieces that hold rows (8-row load
 //     segments, 16-row MFMA fragments): a tile of 20 rows requests 3 KB of
 //     rows per K step where a whole 128-row tile requested 16 KB;

@@ -24,13 +24,12 @@
 namespace cep {
 namespace {
 
-template <int BN, int STAGES, int OCC, bool SWIGLU, bool GATHER>
-__global__ __launch_bounds__(256, OCC) void k_rows_bf16(GemmArgs g) {
-  constexpr int BM = kBf16VarTileM, NW = 4, FN = BN / 32;
+template <bool SWIGLU, bool GATHER>
+__global__ __launch_bounds__(256, 2) void k_rows_bf16(GemmArgs g) {
+  constexpr int BM = kBf16VarTileM, BN = 128, STAGES = 2, NW = 4, FN = BN / 32;
   static_assert(BM == 32 * NW, "a wave owns 32 rows");
   constexpr int A_LD = BM / 8 / NW, B_LD = BN / 8 / NW;
-  constexpr int PER_MAX = A_LD + B_LD;
-  static_assert(STAGES >= 2 && STAGES <= 4 && FN % 2 == 0, "wait counts, gate/up pairs");
+  static_assert(FN % 2 == 0, "gate/up pairs");
   int mt, nt;
   if (!deal_item(*g.n_tiles, g.N / BN, &mt, &nt)) return;
   const Tile t = g.tiles[mt];
@@ -53,7 +52,6 @@ __global__ __launch_bounds__(256, OCC) void k_rows_bf16(GemmArgs g) {
   // which holds chunk (l % 8) ^ ((row >> 1) & 7)
   const int n_seg = (rows + 7) >> 3;
   const int n_a = n_seg > wid ? (n_seg - wid + NW - 1) / NW : 0;
-  const int per = n_a + B_LD;  // loads a step
   const int ch = (lane & 7) ^ ((lane >> 4) & 3);  // chunk in an even segment; odd: ch ^ 4
   const char *arow[A_LD];
   if constexpr (GATHER) {
@@ -89,9 +87,7 @@ __global__ __launch_bounds__(256, OCC) void k_rows_bf16(GemmArgs g) {
               __builtin_amdgcn_readfirstlane(lds_offset(&sB[buf][seg * 64])));
     }
   };
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nk) stage(s, s);
+  stage(0, 0);
 
   const bool mine = wid * 32 < rows;
   f32x16 acc[FN];
@@ -99,16 +95,11 @@ __global__ __launch_bounds__(256, OCC) void k_rows_bf16(GemmArgs g) {
   for (int j = 0; j < FN; ++j) acc[j] = f32x16{};
   const int rsw = ((lane & 31) >> 1) & 7;
   for (int kt = 0; kt < nk; ++kt) {
-    // this wave's loads of step kt are done when at most the loads of the
-    // steps issued after it are outstanding
-    const int later = min(nk - 1, kt + STAGES - 2) - kt;
-    if (later > 0)
-      wait_vmcnt_upto<0, (STAGES - 2) * PER_MAX>(later * per);
-    else
-      wait_vmcnt<0>();
+    // this wave's loads of step kt are its only ones outstanding
+    wait_vmcnt<0>();
     // every wave's loads of step kt landed; step kt-1 fully consumed
     __builtin_amdgcn_s_barrier();
-    if (kt + STAGES - 1 < nk) stage(kt + STAGES - 1, (kt + STAGES - 1) % STAGES);
+    if (kt + 1 < nk) stage(kt + 1, (kt + 1) % STAGES);
     if (!mine) continue;
     const int buf = kt % STAGES;
     bf16x8 a[4], b[4][FN];
@@ -152,11 +143,11 @@ __global__ __launch_bounds__(256, OCC) void k_rows_bf16(GemmArgs g) {
   }
 }
 
-template <int BN, int STAGES, int OCC, bool SWIGLU, bool GATHER>
+template <bool SWIGLU, bool GATHER>
 hipError_t launch_as(const GemmArgs &g, int grid_tiles, hipStream_t s) {
-  if (g.N % BN || g.K % 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_rows_bf16<BN, STAGES, OCC, SWIGLU, GATHER>),
-                     dim3(deal_grid(grid_tiles, g.N / BN)), dim3(256), 0, s, g);
+  if (g.N % 128 || g.K % 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_rows_bf16<SWIGLU, GATHER>), dim3(deal_grid(grid_tiles, g.N / 128)),
+                     dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
@@ -167,10 +158,10 @@ hipError_t launch_bf16_mid(const GemmArgs &g, int grid_tiles, hipStream_t s) {
   if constexpr (SWIGLU) {
     if (g.A == nullptr) {
       if (!g.xrow || !g.perm || g.k < 1) return hipErrorInvalidValue;
-      return launch_as<128, 2, 2, true, true>(g, grid_tiles, s);
+      return launch_as<true, true>(g, grid_tiles, s);
     }
   }
-  return launch_as<128, 2, 2, SWIGLU, false>(g, grid_tiles, s);
+  return launch_as<SWIGLU, false>(g, grid_tiles, s);
 }
 template hipError_t launch_bf16_mid<true>(const GemmArgs &, int, hipStream_t);
 template hipError_t launch_bf16_mid<false>(const GemmArgs &, int, hipStream_t);

@@ -1130,8 +1130,9 @@ CEP_API int cep_ffn_noalloc(cep_ctx *c, int replica, int n_rows, int n_pairs,
     const bool split = c->wk == kWBf16 && A == kBf16TileM;
     const int split_tiles = split ? 2 * E : 0;
     const int tiles = std::min(tiles_cap, batch_tiles(A, list2, P, E));
-    HIPCHK(c, launch_route(a, sc, in_route ? &g : nullptr, cfg.max_tokens_per_replica, xrb, 0, n_rows, k, E, A, P, mpad, tiles_cap, 0, cfg.x_dtype, c->wk,
-                           d, split ? c->n_cu : 0, 2 * I / kBf16TileN, list2, c->d_err, s));
+    HIPCHK(c, launch_route(a, sc, in_route ? &g : nullptr, cfg.max_tokens_per_replica, xrb, 0,
+                           n_rows, k, E, A, P, mpad, tiles_cap, 0, cfg.x_dtype, c->wk, d,
+                           split ? c->n_cu : 0, 2 * I / kBf16TileN, list2, c->d_err, s));
     BlobTable bt{};
     for (int e = 0; e < E; ++e) bt.blob[e] = c->w_res + (size_t)e * c->L.bytes;
     const Arena *gather = packed ? nullptr : &a;
