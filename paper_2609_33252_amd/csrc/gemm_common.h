@@ -364,11 +364,7 @@ __device__ inline int store_y_bf16_staged(const uint32_t (&yb)[8][4][2], const G
 // four dwords hit distinct banks), then the workgroup stores whole 128-byte
 // row segments with 16-byte stores.  st holds BM x 128 bytes.  Barriers and
 // padding rows as in store_y_bf16_staged.
-//
-// SKIP names the kernel that calls it: a function that two kernels share is
-// optimised before it is inlined, and the skipping e4m3 GEMM1 then spills (16
-// experts of 700 rows 366 -> 385 us).
-template <int NW, bool SKIP = false>
+template <int NW>
 __device__ inline void store_h_mx_staged(const f32x4 (&acc)[8][4], const GemmArgs &g,
                                          const Tile &t, int nt, int wm, int wn, int lane,
                                          int tid, u32x4 *st) {

@@ -71,6 +71,16 @@ __device__ inline f32x4 f8_mfma(const i32x8 &w, const i32x8 &x, int ox, int sx) 
 // loads issued before them have landed) and moves on.
 //
 // Epilogues: store_h_mx_staged (GEMM1) and store_y_bf16_staged (GEMM2).
+
+// Rounds of the grid up to which GEMM1 skips the empty row fragments of partly
+// filled tiles.  A workgroup that skips runs ahead of those that share its
+// panels, which are then read again.  16 experts, d 7168, I 2048, GEMM1 without
+// and with, and its HBM reads: 325 rows per expert (two rounds) 247 -> 236 us,
+// 600 -> 930 MB; 520 rows (three) 350 -> 341 us; 700 rows 375 -> 366 us, 890 ->
+// 1190 MB; 780 rows (four) 472 -> 487 us; 900 rows 478 -> 478 us, 958 -> 1340 MB;
+// 1160 and 1670 rows equal, 1250 -> 1790 and 1600 -> 2460 MB.
+constexpr int kSkipRounds = 3;
+
 struct F8Tile {
   Tile t;
   int nt;
@@ -78,7 +88,7 @@ struct F8Tile {
   const float *bs;
 };
 
-template <bool SWIGLU, bool SKIP>
+template <bool SWIGLU>
 __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
   constexpr int NW = 8, STAGES = 2;
   constexpr int BM = 128 * NW / 4, BN = 256, BK = 128, WN = BN / 4;
@@ -208,8 +218,9 @@ __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
 
-    // this wave's row fragments that hold rows
-    const int nfr = (cur.t.rows - wm * 128 + 15) >> 4;
+    // this wave's row fragments that hold rows, or all of them (kSkipRounds)
+    const int nfr = SWIGLU && n_live * ntn > kSkipRounds * (int)gridDim.x
+                        ? 8 : (cur.t.rows - wm * 128 + 15) >> 4;
     auto k_step = [&](int kb, auto part_c) {
       constexpr bool PART = decltype(part_c)::value;
       // this wave's loads of step kb are done when at most the loads of the
@@ -248,11 +259,11 @@ __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
         for (int j = 0; j < 4; ++j) acc[i][j] += p[j] * (j < 2 ? sb0 : sb1);
       }
     };
-    // SKIP: a wave whose row fragments are not all in use runs a K loop of its
+    // GEMM1: a wave whose row fragments are not all in use runs a K loop of its
     // own that skips them (a test per fragment in the common loop costs full
     // tiles their schedule and 24 more spilled registers; GEMM2, with its
     // shorter K loop, lost 15 % to the second loop's registers)
-    if (!SKIP || nfr >= 8) {
+    if (!SWIGLU || nfr >= 8) {
       for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::false_type{});
     } else {
       for (int kb = 0; kb < nkb; ++kb) k_step(kb, std::true_type{});
@@ -290,7 +301,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
                       sizeof(sB[1]) >= 64 * 512, "staging fits buffer 1");
     int n_st = S_EPI;
     if constexpr (SWIGLU)
-      store_h_mx_staged<NW, SKIP>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
+      store_h_mx_staged<NW>(acc, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0]);
     else
       n_st = store_y_bf16_staged<NW>(yb, g, cur.t, cur.nt, wm, wn, lane, tid, &sA[1][0], &sB[1][0],
                                      &sD[db][0]);
@@ -314,24 +325,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm_fp8(GemmArgs g) {
 
 }  // namespace
 
-// Rounds of work items (by the host's bound on M tiles) up to which GEMM1 skips
-// the empty row fragments of partly filled tiles.  A workgroup that skips runs
-// ahead of those that share its panels, which are then read again.  16 experts,
-// d 7168, I 2048, GEMM1 without and with, and its HBM reads (the bound's rounds):
-// 325 rows per expert (2.3) 247 -> 236 us, 600 -> 930 MB; 520 rows (3.1) 350 ->
-// 341 us; 700 rows (3.8) 375 -> 366 us, 890 -> 1190 MB; 780 rows (4.1) 472 -> 487
-// us; 900 rows (4.6) 478 -> 478 us, 958 -> 1340 MB; 1160 and 1670 rows equal,
-// 1250 -> 1790 and 1600 -> 2460 MB; 2200 rows (9.6) 1086 -> 1090 us.
-constexpr int kSkipRounds = 4;
-
 template <bool SWIGLU>
 hipError_t launch_fp8(const GemmArgs &g, int grid_tiles, hipStream_t s) {
   if (g.N % 256 || g.K % 128 || g.K > kMaxDim || g.s_ld % 256) return hipErrorInvalidValue;
-  const int items = balanced_grid(grid_tiles, kGroupM, g.N / 256), cu = persistent_grid();
-  if (SWIGLU && grid_tiles * (g.N / 256) <= kSkipRounds * cu)
-    hipLaunchKernelGGL((k_gemm_fp8<SWIGLU, SWIGLU>), dim3(std::min(items, cu)), dim3(512), 0, s, g);
-  else
-    hipLaunchKernelGGL((k_gemm_fp8<SWIGLU, false>), dim3(std::min(items, cu)), dim3(512), 0, s, g);
+  const int grid = balanced_grid(grid_tiles, kGroupM, g.N / 256);
+  hipLaunchKernelGGL((k_gemm_fp8<SWIGLU>), dim3(std::min(grid, persistent_grid())), dim3(512), 0,
+                     s, g);
   return hipGetLastError();
 }
 

@@ -88,7 +88,7 @@ PLANS = [
     ("fp8_fetch_d6144", dict(d=256, I=512, E=8, Eg=16, k=4), 800, "64", "64"),
     ("fp8_fetch_d6144", dict(d=256, I=2560, E=8, Eg=16, k=4), 640, "256", "160"),
     ("fp8_fetch_d6144", dict(d=256, I=2560, E=8, Eg=16, k=4, fetch_frac=0.25), 640, "256", "160"),
-    # 256-row tiles either side of the four rounds of work items up to which GEMM1
+    # 256-row tiles either side of the three rounds of work items up to which GEMM1
     # skips empty row fragments (500 and 600 rows per expert, 20 column tiles)
     ("fp8_fetch_d6144", dict(d=256, I=2560, E=16, Eg=32, k=4), 2000, "256", "160"),
     ("fp8_fetch_d6144", dict(d=256, I=2560, E=16, Eg=32, k=4), 2400, "256", "160"),
