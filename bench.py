@@ -62,10 +62,10 @@ GEMM_SOURCES = {
     "mxfp4": ["paper_2609_33252_amd/csrc/gemm_mx.hip", "paper_2609_33252_amd/csrc/gemm_common.h"],
 }
 TRAFFIC_BYTES = {  # workload -> (GEMM family, sha1 prefix of its sources, bytes per launch)
-    "fp8_fetch_d6144": ("fp8", "79994b87ed3e", 2200414617),
-    "sync_d4096": ("bf16", "74f40a015eaf", 504284569),
-    "zipf_imbalanced_d7168/per_chunk": ("bf16", "74f40a015eaf", 507444736),
-    "mxfp4_dsv4flash_d4096": ("mxfp4", "25194935b7b2", 1744350003),
+    "fp8_fetch_d6144": ("fp8", "abf46700c06e", 1832346734),
+    "sync_d4096": ("bf16", "1f8d7a97a278", 504274103),
+    "zipf_imbalanced_d7168/per_chunk": ("bf16", "1f8d7a97a278", 507342875),
+    "mxfp4_dsv4flash_d4096": ("mxfp4", "0e44c1b8e664", 1737744603),
 }
 
 

@@ -206,7 +206,8 @@ int cep_begin_layer(cep_ctx *ctx, uint32_t generation, int n_replicas,
  * while an expert without resident weights has no fetch this layer: the
  * chunk is recorded and stays pending (cep_weight_fetch, then cep_flush,
  * launch it).  Ids outside [-1, E) or a wrong n_pairs are detected on the
- * device and reported by cep_get_status. */
+ * device and reported by cep_get_status; the output rows of a batch with a
+ * wrong n_pairs are undefined. */
 int cep_submit_chunk(cep_ctx *ctx, uint32_t generation, int replica, int n_rows, int n_pairs,
                      const int32_t *token_idx, const void *x, const int32_t *topk_id,
                      const float *topk_w, hipEvent_t arrival, int64_t *chunk_id);
